@@ -1,0 +1,31 @@
+"""Stage shapes at the edges of the kernels' tiles and dispatch rules: every
+task of a few mini-batches against the oracle's recomputation of it, in both
+metrics and at the bounds of the stepwise tests."""
+import pytest
+
+import synth
+from stepwise import run_stepwise
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _run(kind, dtype, head, batch, layers, dims, lr, k=1, N=3, steps=5):
+    spec = synth.StageSpec(kind, dtype, head, k, N, batch, layers, dims, lr, 0.9)
+    name = f"{kind}-{dtype}-{head}-b{batch}-l{layers}-{'x'.join(map(str, dims))}"
+    print(f"[shapes] {name}", flush=True)
+    # forced: float32 masks flip too where a unit lies within a rounding of zero
+    worst = run_stepwise(synth.Workload(name, (spec,), steps), steps, torch, forced=True)
+    print(f"[shapes] {name}: {worst.report()}", flush=True)
+
+
+# dims (in, out, hidden). One value in one layer; 32 x 32 tiles with remainders
+# and K below one wave's share; the same with leading dimensions and extents
+# that no 16-byte load fits; products past the short kernel's limit, whole
+# tiles and split K, then ragged 64 x 64 tiles without and with vector loads.
+@pytest.mark.parametrize("head,batch,layers,dims", [
+    ("none", 1, 1, (1, 1, 1)), ("ce", 31, 2, (64, 10, 36)), ("ce", 33, 2, (131, 7, 65)),
+    ("none", 128, 2, (1024, 256, 1024)), ("none", 67, 2, (1027, 259, 514)), ("ce", 130, 2, (516, 1000, 1036)),
+])
+def test_float32_products(head, batch, layers, dims):
+    _run("fc", "fp32", head, batch, layers, dims, 1e-2)
