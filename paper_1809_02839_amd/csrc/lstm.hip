@@ -37,24 +37,35 @@ __device__ __forceinline__ bf16x8_t ld8(const bf16_t* p) {
   return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(p));
 }
 
+// The lane's 8 k of the fragment at k: row[k .. k + 7], row already offset by
+// the lane's quarter kq. TAIL (K not a multiple of 32): zero past K; a kernel
+// argument's worth of test per load would split the batches of loads, so
+// whole fragments are compiled without it.
+template <bool TAIL>
+__device__ __forceinline__ bf16x8_t ld8_k(const bf16_t* row, int k, int kq, int K) {
+  if (!TAIL || k + kq < K) return ld8(row + k);
+  return __builtin_bit_cast(bf16x8_t, u16x8_t{0, 0, 0, 0, 0, 0, 0, 0});
+}
+
 // One wave's share of a 16 x 16 tile: acc[r] = sum_k A[row][k] * Bm[col][k]
 // over the 32-wide k fragments f = CHUNK (wave + WAVES j) + q (q < CHUNK) of
-// K (a multiple of 32), where lane l supplies row l % 16 of A (arow) and
-// column l % 16 of Bm (brow), both already offset by the lane's k quarter.
+// K (a multiple of 8), where lane l supplies row l % 16 of A (arow) and
+// column l % 16 of Bm (brow), both already offset by the lane's k quarter kq
+// (the quarters of the last fragment past K are zero).
 // Every chunk's loads are issued before its MFMAs, so a wave waits for one
 // round of loads per chunk. Lane l ends with rows 4 (l / 16) + r of column
 // l % 16 of its partial sum.
-template <int WAVES>
-__device__ __forceinline__ f32x4_t contract16(const bf16_t* arow, const bf16_t* brow, int K, int wave) {
-  const int nf = K / 32;
+template <int WAVES, bool TAIL>
+__device__ __forceinline__ f32x4_t contract16(const bf16_t* arow, const bf16_t* brow, int K, int kq, int wave) {
+  const int nf = (K + 31) / 32;
   f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
   for (int f0 = wave * CHUNK; f0 < nf; f0 += WAVES * CHUNK) {
     bf16x8_t a[CHUNK], b[CHUNK];
 #pragma unroll
     for (int q = 0; q < CHUNK; ++q)
       if (f0 + q < nf) {
-        a[q] = ld8(arow + 32 * (f0 + q));
-        b[q] = ld8(brow + 32 * (f0 + q));
+        a[q] = ld8_k<TAIL>(arow, 32 * (f0 + q), kq, K);
+        b[q] = ld8_k<TAIL>(brow, 32 * (f0 + q), kq, K);
       }
 #pragma unroll
     for (int q = 0; q < CHUNK; ++q)
@@ -68,10 +79,10 @@ __device__ __forceinline__ f32x4_t contract16(const bf16_t* arow, const bf16_t* 
 // of Bm (already offset by the lane's k quarter). Each A and Bm fragment is
 // loaded once for the two tiles that use it. Lane l ends with rows
 // 16 i + 4 (l / 16) + r of column 16 j + l % 16 in acc[i][j][r].
-template <int WAVES>
+template <int WAVES, bool TAIL>
 __device__ __forceinline__ void contract32(const bf16_t* const (&arow)[2], const bf16_t* const (&brow)[2], int K,
-                                           int wave, f32x4_t (&acc)[2][2]) {
-  const int nf = K / 32;
+                                           int kq, int wave, f32x4_t (&acc)[2][2]) {
+  const int nf = (K + 31) / 32;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -83,8 +94,8 @@ __device__ __forceinline__ void contract32(const bf16_t* const (&arow)[2], const
       if (f0 + q < nf) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          a[i][q] = ld8(arow[i] + 32 * (f0 + q));
-          b[i][q] = ld8(brow[i] + 32 * (f0 + q));
+          a[i][q] = ld8_k<TAIL>(arow[i], 32 * (f0 + q), kq, K);
+          b[i][q] = ld8_k<TAIL>(brow[i], 32 * (f0 + q), kq, K);
         }
       }
 #pragma unroll
@@ -117,6 +128,7 @@ __device__ __forceinline__ void reduce_tile(const f32x4_t& acc, float (*red)[16]
 }
 
 // Block (bx, by): batch rows FWD_ROWS by .., units FWD_UNITS bx ..
+template <bool TAIL>
 __global__ __launch_bounds__(64 * FWD_WAVES) void lstm_step_fwd_kernel(const float* zx_t, const bf16_t* h_prev,
                                                                        const bf16_t* Wh, const float* c_prev, int B,
                                                                        int H, float* gates_t, float* c_t,
@@ -148,7 +160,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES) void lstm_step_fwd_kernel(const flo
       brow[i] = Wh + static_cast<long>((col & 3) * H + u0 + (col >> 2)) * H + kq;
     }
     f32x4_t acc[2][2];
-    contract32<FWD_WAVES>(arow, brow, H, wave, acc);
+    contract32<FWD_WAVES, TAIL>(arow, brow, H, kq, wave, acc);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -195,7 +207,7 @@ __global__ __launch_bounds__(64 * BWD_WAVES) void lstm_step_bwd_kernel(const bf1
   const long H4 = 4L * H;
   // the cell's own operands are loaded first so their latency overlaps the contraction
   const int crow = r0 + tid / BWD_UNITS, cuu = tid % BWD_UNITS, cu = u0 + cuu;
-  const bool cell = tid < 16 * BWD_UNITS && crow < B;
+  const bool cell = tid < 16 * BWD_UNITS && crow < B && cu < H;
   const long t1 = static_cast<long>(crow) * H + cu;
   float gi = 0.0f, gf = 0.0f, gg = 0.0f, go = 0.0f, ct = 0.0f, cpv = 0.0f, dcv = 0.0f, dho = 0.0f;
   if (cell) {
@@ -206,15 +218,18 @@ __global__ __launch_bounds__(64 * BWD_WAVES) void lstm_step_bwd_kernel(const bf1
     go = gr[3 * H];
     ct = c_t[t1];
     if (c_prev) cpv = c_prev[t1];
-    dcv = dc[t1];
+    if (dz_next) dcv = dc[t1];   // the last time step starts the carry
     dho = bf16_to_f32(dh_out[t1]);
   }
   if (dz_next) {
     // dh_rec[row][u0 + n] = sum_k dz_{t+1}[row][k] W_h[k][u0 + n] = sum_k dz[row][k] W_h^T[u0 + n][k]
     const int kq = 8 * (lane >> 4), row = r0 + (lane & 15);
     const bf16_t* arow = dz_next + static_cast<long>(row < B ? row : 0) * H4 + kq;
-    const bf16_t* brow = WhT + static_cast<long>(u0 + (lane & 15)) * H4 + kq;
-    reduce_tile<BWD_WAVES>(contract16<BWD_WAVES>(arow, brow, static_cast<int>(H4), wave), red, dhs, wave, lane, tid);
+    const int unit = u0 + (lane & 15);   // a unit past H reads unit 0 and is never read back
+    const bf16_t* brow = WhT + static_cast<long>(unit < H ? unit : 0) * H4 + kq;
+    // K = 4 H is a multiple of 32 for every H the kernel serves
+    reduce_tile<BWD_WAVES>(contract16<BWD_WAVES, false>(arow, brow, static_cast<int>(H4), kq, wave), red, dhs, wave,
+                           lane, tid);
   }
   if (cell) {
     const float dh = dho + (dz_next ? dhs[crow - r0][cuu] : 0.0f);
@@ -231,28 +246,39 @@ __global__ __launch_bounds__(64 * BWD_WAVES) void lstm_step_bwd_kernel(const bf1
   }
 }
 
-// Y[c][r] = X[r][c] for X [R][C] bf16, R and C multiples of 32; 32 x 32 tiles
-// through LDS (padded rows), 4 elements per thread.
+// Y[c][r] = X[r][c] for X [R][C] bf16; 32 x 32 tiles through LDS (padded
+// rows), 4 elements per thread.
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16_t* X, int R, int C, bf16_t* Y) {
   __shared__ bf16_t tile[32][34];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
   const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
 #pragma unroll
-  for (int j = 0; j < 32; j += 8) tile[ty + j][tx] = X[static_cast<long>(r0 + ty + j) * C + c0 + tx];
+  for (int j = 0; j < 32; j += 8)
+    if (r0 + ty + j < R && c0 + tx < C) tile[ty + j][tx] = X[static_cast<long>(r0 + ty + j) * C + c0 + tx];
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < 32; j += 8) Y[static_cast<long>(c0 + ty + j) * R + r0 + tx] = tile[tx][ty + j];
+  for (int j = 0; j < 32; j += 8)
+    if (c0 + ty + j < C && r0 + tx < R) Y[static_cast<long>(c0 + ty + j) * R + r0 + tx] = tile[tx][ty + j];
 }
 
 }  // namespace
 
-bool lstm_step_supported(int B, int H) { return B >= 1 && B <= 64 && H >= 32 && H % 32 == 0; }
+// Where one fused launch per step beats a GEMM and a cell launch. A fused step
+// re-reads its operands per 32 (16) batch rows, so its time grows with B H
+// once the grid is more than one block per CU; the GEMM path is a flat 30 us
+// (forward) until its own grid fills the chip. Both measured, us per step of a
+// one-layer stage, T = 16: H = 1024: B = 128 672 against 787, B = 192 914
+// against 880; H = 512: B = 100 282 against 632, B = 384 599 against 717;
+// H = 256: B = 512 340 against 614. The line is 160 rows at H = 1024.
+bool lstm_step_supported(int B, int H) {
+  return B >= 1 && H >= 8 && H % 8 == 0 && static_cast<long>(B) * H <= 160L * 1024;
+}
 
 hipError_t lstm_step_fwd(const float* zx_t, const bf16_t* h_prev, const bf16_t* Wh, const float* c_prev, int B,
                          int H, float* gates_t, float* c_t, bf16_t* h_t, hipStream_t s) {
   if (!lstm_step_supported(B, H)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(lstm_step_fwd_kernel, dim3(H / FWD_UNITS, (B + FWD_ROWS - 1) / FWD_ROWS), dim3(64 * FWD_WAVES), 0, s, zx_t,
-                     h_prev, Wh, c_prev, B, H, gates_t, c_t, h_t);
+  auto* kernel = H % 32 ? lstm_step_fwd_kernel<true> : lstm_step_fwd_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3(H / FWD_UNITS, (B + FWD_ROWS - 1) / FWD_ROWS), dim3(64 * FWD_WAVES), 0, s, zx_t, h_prev, Wh, c_prev, B, H, gates_t, c_t, h_t);
   return hipGetLastError();
 }
 
@@ -260,14 +286,14 @@ hipError_t lstm_step_bwd(const bf16_t* dz_next, const bf16_t* WhT, const bf16_t*
                          const float* c_t, const float* c_prev, int B, int H, float* dc, bf16_t* dz_t,
                          hipStream_t s) {
   if (!lstm_step_supported(B, H)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(lstm_step_bwd_kernel, dim3(H / BWD_UNITS, (B + 15) / 16), dim3(64 * BWD_WAVES), 0, s, dz_next,
+  hipLaunchKernelGGL(lstm_step_bwd_kernel, dim3((H + BWD_UNITS - 1) / BWD_UNITS, (B + 15) / 16), dim3(64 * BWD_WAVES), 0, s, dz_next,
                      WhT, dh_out, gates_t, c_t, c_prev, B, H, dc, dz_t);
   return hipGetLastError();
 }
 
 hipError_t transpose_bf16(const bf16_t* X, int R, int C, bf16_t* Y, hipStream_t s) {
-  if (R % 32 || C % 32 || R <= 0 || C <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(transpose_bf16_kernel, dim3(C / 32, R / 32), dim3(256), 0, s, X, R, C, Y);
+  if (R <= 0 || C <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(transpose_bf16_kernel, dim3((C + 31) / 32, (R + 31) / 32), dim3(256), 0, s, X, R, C, Y);
   return hipGetLastError();
 }
 

@@ -1341,7 +1341,7 @@ void Stage::bwd_tfm(int slot, const void* dy, void* dx) {
 // 3 layer output u_{l+1} (bf16); id 4L: dlogits (bf16) with a CE head.
 // workspace: 0 zx (f32), 1 logits (f32), 2/3 du ping-pong, 4 dz (bf16),
 // 5 dh_rec (f32), 6 dc (f32), 7 row losses, 8 W_h^T (bf16, fused steps),
-// 9 partials. With B <= 64 and H a multiple of 32 every recurrent step is one
+// 9 partials. Up to the batch of lstm_step_supported every recurrent step is one
 // fused launch (contraction + cell); otherwise a GEMM and a cell launch.
 void Stage::fwd_lstm(int slot, const void* x, void* y, const int32_t* labels, float* loss) {
   const int L = d_.num_layers, B = d_.batch, I = d_.dims[0], H = d_.dims[1], T = d_.dims[2], V = d_.dims[3];
@@ -1423,8 +1423,8 @@ void Stage::bwd_lstm(int slot, const void* dy, void* dx) {
     const float* gates = stash<float>(slot, q);
     const float* c = stash<float>(slot, q + 1);
     const bf16_t* hs = stash<bf16_t>(slot, q + 2);
-    LAUNCH("clear_dc", 0, 4.0 * B * H, fill_f32(dc, 0.0f, static_cast<long>(B) * H, s_));
     const bool fused = lstm_step_supported(B, H);
+    if (!fused) LAUNCH("clear_dc", 0, 4.0 * B * H, fill_f32(dc, 0.0f, static_cast<long>(B) * H, s_));
     if (fused) {
       bf16_t* whT = ws<bf16_t>(8);
       LAUNCH("transpose", 0, 8.0 * H * H * 2, transpose_bf16(static_cast<const bf16_t*>(wb(p + 1)), 4 * H, H, whT, s_));

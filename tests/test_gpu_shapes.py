@@ -29,3 +29,15 @@ def _run(kind, dtype, head, batch, layers, dims, lr, k=1, N=3, steps=5):
 ])
 def test_float32_products(head, batch, layers, dims):
     _run("fc", "fp32", head, batch, layers, dims, 1e-2)
+
+
+# dims (H, H, T[, vocab]): H no multiple of 32 (short last k fragment) nor of 16
+# (short last unit block of the backward); batches past one row block of either
+# direction with remainders; the largest batch of the fused steps and the first
+# past it (a GEMM and a cell launch per step).
+@pytest.mark.parametrize("head,batch,dims", [
+    ("none", 1, (8, 8, 3, 8)), ("ce", 33, (72, 72, 4, 24)), ("none", 100, (40, 40, 3, 8)), ("none", 65, (1032, 1032, 3, 8)),
+    ("none", 320, (512, 512, 3, 8)), ("none", 321, (512, 512, 3, 8)),
+])
+def test_lstm_steps(head, batch, dims):
+    _run("reslstm", "bf16", head, batch, 2, dims, 1e-2)
