@@ -10,7 +10,12 @@
 
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
+#include <deque>
+#include <mutex>
+#include <system_error>
+#include <thread>
 
 namespace spx {
 
@@ -48,6 +53,117 @@ void PinnedInts::allocate(size_t n) {
 
 PinnedInts::~PinnedInts() {
   if (host_) (void)hipHostFree(host_);
+}
+
+HostCopy::~HostCopy() {
+  for (hipEvent_t e : done_)
+    if (e) (void)hipEventDestroy(e);
+  if (ring_) (void)hipHostFree(ring_);
+}
+
+void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
+                   const std::vector<TensorInfo>& tensors, hipStream_t s) {
+  struct Job {   // arena elements [off, off + n)
+    const float* arena;
+    float* packed;
+    long off, n;
+    size_t slot;
+  };
+  const long total = tensors.empty() ? 0 : tensors.back().off + tensors.back().n;
+  std::vector<Job> jobs;
+  for (const auto& a : arrays)
+    for (long o = 0; o < total; o += SLOT_FLOATS)
+      jobs.push_back({a.first, a.second, o, std::min(SLOT_FLOATS, total - o), jobs.size() % SLOTS});
+  if (!ring_) {
+    hip_check(hipHostMalloc(reinterpret_cast<void**>(&ring_), SLOTS * SLOT_FLOATS * sizeof(float), hipHostMallocDefault),
+              "hipHostMalloc");
+  }
+  for (hipEvent_t& e : done_)
+    if (!e) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
+
+  std::mutex mu;
+  std::condition_variable cv;
+  std::deque<const Job*> ready;      // copied to their slot, to be moved to the destination
+  bool busy[SLOTS] = {};
+  bool end = false;
+  auto move = [&](const Job& j) {   // the tensors' parts of the range, without the arena's padding
+    const float* src = ring_ + j.slot * SLOT_FLOATS;
+    long at = 0;
+    for (const TensorInfo& t : tensors) {
+      const long b = std::max(t.off, j.off), e = std::min(t.off + t.n, j.off + j.n);
+      if (b < e) std::memcpy(j.packed + at + (b - t.off), src + (b - j.off), (e - b) * sizeof(float));
+      at += t.n;
+    }
+  };
+  auto work = [&]() {
+    std::unique_lock<std::mutex> lock(mu);
+    for (;;) {
+      cv.wait(lock, [&] { return end || !ready.empty(); });
+      if (ready.empty()) return;
+      const Job* j = ready.front();
+      ready.pop_front();
+      lock.unlock();
+      move(*j);
+      lock.lock();
+      busy[j->slot] = false;
+      cv.notify_all();
+    }
+  };
+  std::vector<std::thread> threads;
+  struct Joiner {                    // also where a copy below fails
+    std::mutex& mu;
+    std::condition_variable& cv;
+    bool& end;
+    std::vector<std::thread>& t;
+    ~Joiner() {
+      {
+        std::lock_guard<std::mutex> lock(mu);
+        end = true;
+      }
+      cv.notify_all();
+      for (std::thread& x : t) x.join();
+    }
+  } joiner{mu, cv, end, threads};
+  // threads cost about 0.1 ms to start and join: from two full slots on
+  const size_t want = total * static_cast<long>(arrays.size()) < 2 * SLOT_FLOATS ? 0 : std::min<size_t>(4, jobs.size());
+  threads.reserve(want);
+  try {
+    for (size_t i = 0; i < want; ++i) threads.emplace_back(work);
+  } catch (const std::system_error&) {
+    // fewer threads, or none: the calling thread moves the data itself
+  }
+  size_t issued = 0;
+  for (size_t i = 0; i < jobs.size(); ++i) {
+    // keep the ring full ahead of the job awaited next
+    while (issued < jobs.size() && issued < i + SLOTS) {
+      const Job& j = jobs[issued];
+      {
+        std::unique_lock<std::mutex> lock(mu);
+        if (busy[j.slot]) {
+          if (issued > i) break;     // come back for it after handing over the next finished job
+          cv.wait(lock, [&] { return !busy[j.slot]; });
+        }
+        busy[j.slot] = true;
+      }
+      hip_check(hipMemcpyAsync(ring_ + j.slot * SLOT_FLOATS, j.arena + j.off, j.n * sizeof(float),
+                               hipMemcpyDeviceToHost, s),
+                "copy to host");
+      hip_check(hipEventRecord(done_[j.slot], s), "hipEventRecord");
+      ++issued;
+    }
+    const Job& j = jobs[i];
+    hip_check(hipEventSynchronize(done_[j.slot]), "hipEventSynchronize");
+    if (threads.empty()) {
+      move(j);
+      busy[j.slot] = false;
+      continue;
+    }
+    {
+      std::lock_guard<std::mutex> lock(mu);
+      ready.push_back(&j);
+    }
+    cv.notify_all();
+  }
 }
 
 namespace {
@@ -612,17 +728,10 @@ void Stage::set_state(const float* W, const float* v) {
 
 void Stage::get_state(float* W, float* v) {
   sync();
-  std::vector<float> h(n_arena_);
-  for (int which = 0; which < 2; ++which) {
-    float* dst = which == 0 ? W : v;
-    if (!dst) continue;
-    hip_check(hipMemcpy(h.data(), which == 0 ? W_ : v_, n_arena_ * 4, hipMemcpyDeviceToHost), "copy state");
-    long o = 0;
-    for (const TensorInfo& t : tensors_) {
-      std::memcpy(dst + o, h.data() + t.off, t.n * 4);
-      o += t.n;
-    }
-  }
+  std::vector<std::pair<const float*, float*>> arrays;
+  if (W) arrays.emplace_back(W_, W);
+  if (v) arrays.emplace_back(v_, v);
+  host_copy_.run(arrays, tensors_, s_);
 }
 
 void Stage::get_predicted(int slot, float* out) {

