@@ -248,7 +248,7 @@ int spectrain_stage_get_predicted(spectrain_stage_t st, int32_t slot, float* Wha
  * a split GEMM, and the partial planes the update reads in place of g. */
 typedef struct {
   char name[48];        /* kernel family: the kernel's name with its template arguments as a profiler
-                           lists it (e.g. "gemm_bf16_kernel<0, 3, false, 128, 1>"), or a pass name
+                           lists it (e.g. "gemm_bf16_kernel<0, 3, false, 1>"), or a pass name
                            such as "fused_update", "layernorm_bwd", "lstm_step" */
   int64_t launches;
   double ms_total;      /* summed event-to-event duration */

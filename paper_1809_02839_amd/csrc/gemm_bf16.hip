@@ -3,30 +3,24 @@
 // layers, 3x3 convolutions as implicit GEMM (forward, data gradient, filter
 // gradient) and the batched products inside attention.
 //
-// Block tile 128 x 128 (or 128 x 64, see shape_of), K step 64, 256 threads =
-// 4 waves in a 2 x 2 grid, each wave owning a 64 x 64 (64 x 32) sub-tile of
-// 2 x 2 (2 x 1) MFMA tiles of 32 x 32; some convolution gathers (forward, and
-// data gradient against a transposed filter) use 512 threads, two waves per
-// sub-tile that share each K step. K-mode operand
-// tiles are staged in LDS as [row][k] (8 consecutive k per lane make one
-// 16-byte MFMA operand read; the 144-byte row pitch puts eight consecutive
-// rows on disjoint banks); R-mode tiles (rows contiguous in memory) are staged
-// as [k][row] as loaded, with the 16-byte units of each 256-byte k row
-// permuted by an XOR with 4 (k mod 4), and transposed by the LDS reads. In
-// the register-staged kernel (the 128 x 64 tiles) global loads run two K
-// steps ahead of the MFMAs (two register stages, two LDS buffers). All
-// global reads are
-// buffer loads whose resource spans exactly the operand tensor: an offset
-// outside it (zero padding of convolutions, ragged tile edges) reads zero.
+// Block tile 128 x 128, K step 64, 256 threads = 4 waves in a 2 x 2 grid, each
+// wave owning a 64 x 64 sub-tile of 2 x 2 MFMA tiles of 32 x 32; some
+// convolution gathers (forward, and data gradient against a transposed
+// filter) use 512 threads, two waves per sub-tile that share each K step.
+// All global reads are buffer loads whose resource spans exactly the operand
+// tensor: an offset outside it (zero padding of convolutions, ragged tile
+// edges) reads zero.
 //
-// Direct loads (every 128-wide block, 4 or 8 waves): the buffer loads carry the LDS
-// flag, so each lane's 16 bytes go straight into a two-stage LDS ring at the
-// position fixed by its lane number, with no register stage and no LDS store
-// instruction (LDS stores contend with the MFMA operand reads; direct loads
-// measured beside LDS reads do not). The lanes' source addresses are
-// permuted instead of the destinations: K-mode tiles become rows of 64 k
-// without padding whose 16-byte chunks are XOR-swizzled by row pairs, R-mode
-// tiles keep the layout above.
+// Direct loads: the buffer loads carry the LDS flag, so each lane's 16 bytes
+// go straight into a two-stage LDS ring at the position fixed by its lane
+// number, with no register stage and no LDS store instruction (LDS stores
+// contend with the MFMA operand reads; direct loads measured beside LDS reads
+// do not). The lanes' source addresses are permuted instead of the
+// destinations: K-mode operand tiles (8 consecutive k per lane make one
+// 16-byte MFMA operand read) become rows of 64 k without padding whose 16-byte
+// chunks are XOR-swizzled by row pairs; R-mode tiles (rows contiguous in
+// memory) are [k][row] as loaded, with the 16-byte units of each 256-byte k
+// row permuted by an XOR with 4 (k mod 4), and transposed by the LDS reads.
 //
 // Epilogue: an unsplit launch whose output rows allow 16-byte accesses
 // stages its float32 tile in LDS and then gives each thread eight
@@ -40,7 +34,7 @@
 // the MFMA layout, with every epilogue load of a lane issued before its
 // first store.
 //
-// Split-K: a 128 x 128 launch may divide K into `splits` ranges; each writes
+// Split-K: a launch may divide K into `splits` ranges; each writes
 // float32 partial tiles to a workspace and an elementwise pass sums the
 // partials in a fixed order and applies the epilogue, so results do not
 // depend on timing.
@@ -53,10 +47,10 @@ namespace spx {
 namespace {
 
 constexpr int BM = 128, BN = 128, BK = 64, NT = 256;
-constexpr int PITCH = BK + 8;            // K-mode tile [row][k]: bf16 per row (144 bytes)
 constexpr int RPITCH = 128;              // R-mode tile [k][row]: bf16 per k row (256 bytes, swizzled)
-constexpr int TILE_ELEMS = 128 * PITCH;  // one operand tile (K-mode; the R-mode tile needs BK * RPITCH)
-static_assert(TILE_ELEMS >= BK * RPITCH, "both tile layouts fit one operand buffer");
+constexpr int EPI_PITCH = BN + 4;        // float32 tile staged by the epilogue: floats per row
+constexpr int LDS_BYTES = 128 * EPI_PITCH * 4;   // the larger of that tile and two stages of both operand tiles
+static_assert(LDS_BYTES >= 2 * 2 * 128 * BK * 2, "two stages fit");
 
 // Element offset, inside a k row of an R-mode tile, of row (column) c: the
 // 16-byte unit c / 8 is XORed with 4 (k mod 4). A transposing read covers
@@ -72,12 +66,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 
-// MFMA operand (8 consecutive k of one row) from a K-mode tile [row][PITCH].
-__device__ __forceinline__ bf16x8_t frag_k(const bf16_t* s, int row, int k) {
-  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u16x8_t*>(s + row * PITCH + k));
-}
-
-// The same operand from a K-mode tile filled by direct loads: rows of 64 k
+// MFMA operand (8 consecutive k of one row) from a K-mode tile: rows of 64 k
 // without padding, the eight 16-byte chunks of row r permuted by an XOR with
 // (r / 2) % 8. Sixteen lanes reading one chunk of sixteen consecutive rows
 // then hit every bank once (rows 2j and 2j + 1 share a slot but lie in
@@ -137,9 +126,7 @@ struct KArgs {
   float* partial;        // splits > 1: [split][batch][M][N] float32
   int vec_epi;           // output, bias, residual and mask allow the four-column epilogue
   int vec8;              // ... and the eight-column one (N, ldc multiples of 8, 16-byte aligned tensors)
-  int bn;                // block tile width in N (host side: selects the kernel)
   int ksl;               // waves per output sub-tile (host side: selects the kernel)
-  int dma;               // operand tiles loaded directly into LDS (host side: selects the kernel)
   EpiDev e;
 };
 
@@ -149,11 +136,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const bf16_t* p, lon
   if (bytes < 0) bytes = 0;
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), static_cast<short>(0), static_cast<int>(bytes),
                                            BUF_FLAGS);
-}
-
-__device__ __forceinline__ uint4 bload(__amdgpu_buffer_rsrc_t r, int byte_off) {
-  u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // Direct load into LDS: the 16 bytes of lane l land at LDS byte address
@@ -179,19 +161,19 @@ __device__ __forceinline__ void dma_wait() {
 // TAPK (convolutions whose channel count is a multiple of BK): every K step
 // lies inside one filter tap, so the tap and its pixel shift are uniform for
 // the whole block and each vector costs one add and a bounds check.
-template <int MODE, bool TAPK, int ROWS, int NTH, bool DMA = false>
+template <int MODE, bool TAPK, int ROWS, int NTH>
 struct KLoader {
   static constexpr int V = 8 * ROWS / NTH;   // 16-byte vectors per thread
-  static_assert(!DMA || NTH % 128 == 0, "the direct-load chunk permutation assumes 16 | NTH / 8");
+  static_assert(NTH % 128 == 0, "the direct-load chunk permutation assumes 16 | NTH / 8");
   int row_ok[4];
   int base[4];       // byte offset of the row (PLAIN) or of the pixel's channel 0 (CONV)
   int ph[4], pw[4];  // CONV: pixel coordinates
   int kq8;           // this thread's k offset inside a K step
 
   __device__ void init(const OperandDev& o, int row0, int tid, int /*k0*/) {
-    // DMA: vector t + NTH i lands in LDS slot t % 8 of its row, which holds
-    // k chunk slot ^ ((row / 2) % 8) (see frag_kd); row / 2 % 8 = t / 16 % 8
-    kq8 = DMA ? (((tid & 7) ^ ((tid >> 4) & 7)) * 8) : (tid & 7) * 8;
+    // vector t + NTH i lands in LDS slot t % 8 of its row, which holds k chunk
+    // slot ^ ((row / 2) % 8) (see frag_kd); row / 2 % 8 = t / 16 % 8
+    kq8 = ((tid & 7) ^ ((tid >> 4) & 7)) * 8;
 #pragma unroll
     for (int i = 0; i < V; ++i) {
       const int r = row0 + ((tid + NTH * i) >> 3);
@@ -250,36 +232,25 @@ struct KLoader {
     }
   }
 
-  __device__ __forceinline__ void load(const OperandDev& o, __amdgpu_buffer_rsrc_t rs, int k0, uint4 (&reg)[4]) {
-    visit(o, k0, [&](int i, int off) { reg[i] = bload(rs, off); });
-  }
-
-  // DMA: vector i of wave w's lanes lands at tile byte 16 (64 w + NTH i) + 16 lane
+  // vector i of wave w's lanes lands at tile byte 16 (64 w + NTH i) + 16 lane
   __device__ __forceinline__ void dma(const OperandDev& o, __amdgpu_buffer_rsrc_t rs, int k0, uint32_t tile,
                                       int wave) {
     visit(o, k0, [&](int i, int off) { dma16(rs, tile + 16u * (64 * wave + NTH * i), off); });
   }
 
-  __device__ __forceinline__ void store(bf16_t* lds, const uint4 (&reg)[4], int tid) const {
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const int v = tid + NTH * i;
-      *reinterpret_cast<uint4*>(lds + (v >> 3) * PITCH + (v & 7) * 8) = reg[i];
-    }
-  }
 };
 
 // ---- R-mode: 8 consecutive rows of one k ----------------------------------
 // The tile is kept in LDS as [k][row] (rows contiguous, RPITCH elements per k)
-// exactly as loaded, and the MFMA operand reads transpose it (see frag_r).
+// as loaded, and the MFMA operand reads transpose it (see frag_r).
 // With G = ROWS / 8 row groups, thread t of NTH loads row group t % G (rows
 // 8 (t % G) .. + 7) at k = k0 + t / G + (NTH / G) i (i < BK G / NTH): G lanes
 // cover one k row of the tile. Loads must be issued for consecutive K steps
 // (the filter-gradient gather advances its pixel coordinates by BK per call).
-template <int MODE, bool TAPK, int ROWS, int NTH, bool DMA = false>
+template <int MODE, bool TAPK, int ROWS, int NTH>
 struct RLoader {
   static constexpr int G = ROWS / 8, KS = NTH / G, V = BK / KS;
-  static_assert(!DMA || (G == 16 && NTH % 64 == 0), "direct loads fill 256-byte k rows of 128-row tiles");
+  static_assert(G == 16 && NTH % 64 == 0, "direct loads fill 256-byte k rows of 128-row tiles");
   int rows_ok;
   int colb;      // byte offset of the row group (PLAIN, FILTER_T) or of its channel + tap shift (WGRAD)
   int tkh, tkw;  // WGRAD: filter tap of the row group
@@ -288,9 +259,9 @@ struct RLoader {
 
   __device__ void init(const OperandDev& o, int row0, int tid, int k0) {
     kk0 = tid / G;
-    // DMA: vector t + NTH i lands in unit slot t % 16 of its k row, which
+    // vector t + NTH i lands in unit slot t % 16 of its k row, which
     // holds row group slot ^ 4 (k % 4) (rcol); k % 4 = t / 16 % 4
-    const int grp = DMA ? ((tid & 15) ^ (((tid >> 4) & 3) << 2)) : tid % G;
+    const int grp = (tid & 15) ^ (((tid >> 4) & 3) << 2);
     const int r = row0 + grp * 8;
     rows_ok = r < o.rows;  // rows are a multiple of 8
     const uint32_t rr = rows_ok ? r : 0;
@@ -354,28 +325,17 @@ struct RLoader {
     }
   }
 
-  __device__ __forceinline__ void load(const OperandDev& o, __amdgpu_buffer_rsrc_t rs, int k0, uint4 (&reg)[4]) {
-    visit(o, k0, [&](int i, int off) { reg[i] = bload(rs, off); });
-  }
-
   __device__ __forceinline__ void dma(const OperandDev& o, __amdgpu_buffer_rsrc_t rs, int k0, uint32_t tile,
                                       int wave) {
     visit(o, k0, [&](int i, int off) { dma16(rs, tile + 16u * (64 * wave + NTH * i), off); });
   }
 
-  __device__ __forceinline__ void store(bf16_t* lds, const uint4 (&reg)[4], int tid) const {
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      const int k = tid / G + KS * i;
-      *reinterpret_cast<uint4*>(lds + k * RPITCH + rcol(k, (tid % G) * 8)) = reg[i];
-    }
-  }
 };
 
-template <int MODE, bool TAPK, int ROWS, int NTH, bool DMA = false>
+template <int MODE, bool TAPK, int ROWS, int NTH>
 struct LoaderFor {
-  using type = typename std::conditional<(MODE <= OP_K_CONV_DGRAD), KLoader<MODE, TAPK, ROWS, NTH, DMA>,
-                                         RLoader<MODE, TAPK, ROWS, NTH, DMA>>::type;
+  using type = typename std::conditional<(MODE <= OP_K_CONV_DGRAD), KLoader<MODE, TAPK, ROWS, NTH>,
+                                         RLoader<MODE, TAPK, ROWS, NTH>>::type;
 };
 
 // value = acc * alpha + bias + residuals, ReLU, then float32 and/or bf16 stores
@@ -599,9 +559,9 @@ __device__ __forceinline__ void write_tile(const KArgs& args, f32x16_t (&acc)[2]
 // The bf16 operands of the staged epilogue (below) for one thread: the bias
 // of its 8 columns and the residual and mask of its NP row segments (8
 // columns each, rows erl + RPP p of the tile).
-template <int BNT, int NTH>
+template <int NTH>
 struct EpiOperands {
-  static constexpr int TPR = BNT / 8;   // threads per row
+  static constexpr int TPR = BN / 8;   // threads per row
   static constexpr int RPP = NTH / TPR; // rows per pass
   static constexpr int NP = 128 / RPP;  // rows per thread
   uint4 bb, rb[NP], mk[NP];
@@ -630,10 +590,10 @@ struct EpiOperands {
 // tile inside the output: straight-line code whose NP rows the compiler can
 // interleave. The operations and their order are those of epilogue4_values,
 // so both paths give the same bits.
-template <int BNT, int NTH, bool BIAS, bool RES, bool RELU, bool MASK>
-__device__ __forceinline__ void staged_rows(const EpiDev& e, const float* tile, const EpiOperands<BNT, NTH>& eop,
+template <int NTH, bool BIAS, bool RES, bool RELU, bool MASK>
+__device__ __forceinline__ void staged_rows(const EpiDev& e, const float* tile, const EpiOperands<NTH>& eop,
                                             bf16_t* out, int ecl, int erl) {
-  constexpr int EP = BNT + 4, RPP = EpiOperands<BNT, NTH>::RPP, NP = EpiOperands<BNT, NTH>::NP;
+  constexpr int EP = EPI_PITCH, RPP = EpiOperands<NTH>::RPP, NP = EpiOperands<NTH>::NP;
   auto unpack8 = [](uint4 u, float (&f)[8]) {
     const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
@@ -675,30 +635,59 @@ __device__ __forceinline__ void staged_rows(const EpiDev& e, const float* tile, 
   }
 }
 
-// BNT: block tile width in N (128, or 64 for launches whose 128-wide tiles
-// cannot give every CU two blocks); each wave owns 64 x (BNT / 2).
-// KSL: waves per output sub-tile. With KSL = 2 (8 waves, 128-wide tiles
-// only) waves w and w + 4 own the same sub-tile and take the first and the
-// second half of every K step; their accumulators are added through LDS at
-// the end (first half + second half), so one block per CU keeps two waves
-// on every SIMD without the narrow tile's extra operand traffic.
-// DMA (128-wide tiles, 4- or 8-wave blocks): the operand tiles go from
-// global memory straight into a two-stage LDS ring (buffer loads with the
-// LDS flag), with no register stage and no LDS store instruction; a stage is
-// read after its own loads are counted complete and the block has
-// synchronised. A wave that issues its share of a stage's direct loads
+// The same for a plain or biased float32 output, on a tile of which the first
+// `rows` rows lie inside it; out points at the tile's first row in the
+// thread's columns. The vocabulary's scores (8192 x 32000, K = 512), whose
+// 1 GB of stores is most of the launch, took 555 us through the generic rows
+// and take 478. Partial tiles of a K split gained nothing from it (15.0
+// against 15.4 us for the bottleneck's 1x1 filter gradient).
+template <int NTH, bool BIAS>
+__device__ __forceinline__ void staged_rows_f32(const float* tile, uint4 bb, float* out, long ldc, int rows, bool colok,
+                                                int ecl, int erl) {
+  constexpr int EP = EPI_PITCH, RPP = EpiOperands<NTH>::RPP, NP = EpiOperands<NTH>::NP;
+  if (!colok) return;
+  float bias[8];
+  if constexpr (BIAS) {
+    const uint32_t w[4] = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      bias[2 * q] = __uint_as_float(w[q] << 16);
+      bias[2 * q + 1] = __uint_as_float(w[q] & 0xffff0000u);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int rr = erl + p * RPP;
+    float4 a0 = *reinterpret_cast<const float4*>(tile + rr * EP + ecl);
+    float4 a1 = *reinterpret_cast<const float4*>(tile + rr * EP + ecl + 4);
+    if constexpr (BIAS) {
+      a0.x += bias[0]; a0.y += bias[1]; a0.z += bias[2]; a0.w += bias[3];
+      a1.x += bias[4]; a1.y += bias[5]; a1.z += bias[6]; a1.w += bias[7];
+    }
+    if (rr < rows) {
+      float4* o = reinterpret_cast<float4*>(out + static_cast<long>(rr) * ldc);
+      o[0] = a0;
+      o[1] = a1;
+    }
+  }
+}
+
+// KSL: waves per output sub-tile. With KSL = 2 (8 waves) waves w and w + 4
+// own the same sub-tile and take the first and the second half of every K
+// step; their accumulators are added through LDS at the end (first half +
+// second half), so one block per CU keeps two waves on every SIMD.
+// The operand tiles go from global memory straight into a two-stage LDS ring
+// (buffer loads with the LDS flag); a stage is read after its own loads are
+// counted complete and the block has synchronised. A wave that issues its share of a stage's direct loads
 // waits for the memory pipeline to accept them, about as long as its MFMAs
 // of a K step take; on 8-wave blocks the two waves of a SIMD issue half as
 // many loads each and one multiplies while the other waits.
-template <int MA, int MB, bool TAPK, int BNT, int KSL, bool DMA = false>
+template <int MA, int MB, bool TAPK, int KSL>
 __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
-  constexpr int NJ = BNT / 64;   // 32-column MFMA tiles per wave
+  constexpr int NJ = 2;          // 32-column MFMA tiles per wave
   constexpr int NTH = NT * KSL;
   constexpr int KW = BK / KSL;   // k of each K step that one wave multiplies
-  static_assert(KSL == 1 || BNT == 128, "K-sliced waves use the 128-wide tile");
-  static_assert(!DMA || BNT == 128, "direct loads serve the 128-wide tile");
-  static_assert(KSL == 1 || DMA, "8-wave blocks load their operands directly");
-  __shared__ __attribute__((aligned(16))) bf16_t lds[2][2][TILE_ELEMS];  // [buffer][A|B]
+  __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_BYTES / 2];
 
   const int tid = threadIdx.x;
   // XCD-aware tile order: consecutive blocks land on consecutive XCDs; give
@@ -720,7 +709,7 @@ __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
     tile = (bid & 7) * (args.tiles_total >> 3) + (bid >> 3);
   }
   const int tm = tile / args.tiles_n, tn = tile - tm * args.tiles_n;
-  const int row0 = tm * BM, col0 = tn * BNT;
+  const int row0 = tm * BM, col0 = tn * BN;
 
   const int z = zs / args.splits, split = zs - z * args.splits;
   const int z1 = z / args.zdiv, z2 = z - z1 * args.zdiv;
@@ -735,22 +724,20 @@ __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
   const int kend = min(args.K, kbeg + args.k_per_split);
   const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
 
-  typename LoaderFor<MA, TAPK, BM, NTH, DMA>::type la;
-  typename LoaderFor<MB, TAPK, BNT, NTH, DMA>::type lb;
+  typename LoaderFor<MA, TAPK, BM, NTH>::type la;
+  typename LoaderFor<MB, TAPK, BN, NTH>::type lb;
   la.init(A, row0, tid, kbeg);
   lb.init(B, col0, tid, kbeg);
 
-  // The staged epilogue's operands do not depend on the product: the
-  // direct-load 4-wave kernels, which hold no operand tiles in registers,
-  // issue their loads before the first K step so that they arrive while the
-  // block multiplies (the register-staged loop, and the 8-wave blocks with
-  // half the registers per wave, have none to spare for them and load them
-  // in the epilogue). Issued before the first direct loads, they are older
+  // The staged epilogue's operands do not depend on the product: the 4-wave
+  // kernels issue their loads before the first K step so that they arrive
+  // while the block multiplies (the 8-wave blocks, with half the registers
+  // per wave, have none to spare for them and load them in the epilogue). Issued before the first direct loads, they are older
   // than every stage the K loop waits for.
   const bool staged_epi = args.splits == 1 && args.vec8;
   const long coff = z1 * args.c_bs1 + z2 * args.c_bs2;
-  EpiOperands<BNT, NTH> eop;
-  if constexpr (DMA && KSL == 1) {
+  EpiOperands<NTH> eop;
+  if constexpr (KSL == 1) {
     if (staged_epi) eop.load(args, row0, col0, tid, coff);
   }
 
@@ -777,13 +764,12 @@ __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
         fa[i] = (MA <= OP_K_CONV_DGRAD)
-                    ? (DMA ? frag_kd(sa, wm * 64 + i * 32 + (lane & 31), kl) : frag_k(sa, wm * 64 + i * 32 + (lane & 31), kl))
+                    ? frag_kd(sa, wm * 64 + i * 32 + (lane & 31), kl)
                     : frag_r(sa, wm * 64 + i * 32, kk, lane);
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         fb[j] = (MB <= OP_K_CONV_DGRAD)
-                    ? (DMA ? frag_kd(sb, wn * (32 * NJ) + j * 32 + (lane & 31), kl)
-                           : frag_k(sb, wn * (32 * NJ) + j * 32 + (lane & 31), kl))
+                    ? frag_kd(sb, wn * (32 * NJ) + j * 32 + (lane & 31), kl)
                     : frag_r(sb, wn * (32 * NJ) + j * 32, kk, lane);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -795,76 +781,41 @@ __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
     if constexpr (MA == OP_K_CONV_DGRAD && MB == OP_R_FILTER_T) __builtin_amdgcn_s_setprio(0);
   };
 
-  if constexpr (DMA) {
-    if (nk > 0) {
-      // stage b (b = 0, 1) at elements [2 b BK 128, ...): A tile then B tile,
-      // 128 x 64 each; the prefetch of the two steps past the end reads zeros
-      // or data that is never multiplied, and is drained before the LDS is
-      // reused by the epilogue
-      constexpr int TE = BM * BK, SE = 2 * TE;
-      static_assert(sizeof(lds) >= 2 * SE * sizeof(bf16_t), "two stages fit the operand buffers");
-      constexpr int VS = decltype(la)::V + decltype(lb)::V;   // direct loads per thread per stage
-      bf16_t* const l0 = &lds[0][0][0];
-      const uint32_t lbase = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) bf16_t*)l0));
-      const int wv = __builtin_amdgcn_readfirstlane(wave);
-      auto issue = [&](int buf, int k0) {
-        const uint32_t t = lbase + static_cast<uint32_t>(buf * SE * 2);
-        la.dma(A, ra, k0, t, wv);
-        lb.dma(B, rb, k0, t + TE * 2, wv);
-      };
-      issue(0, kbeg);
-      issue(1, kbeg + BK);
+  if (nk > 0) {
+    // stage b (b = 0, 1) at elements [2 b BK 128, ...): A tile then B tile,
+    // 128 x 64 each; the prefetch of the two steps past the end reads zeros
+    // or data that is never multiplied, and is drained before the LDS is
+    // reused by the epilogue
+    constexpr int TE = BM * BK, SE = 2 * TE;
+    static_assert(sizeof(lds) >= 2 * SE * sizeof(bf16_t), "two stages fit the operand buffers");
+    constexpr int VS = decltype(la)::V + decltype(lb)::V;   // direct loads per thread per stage
+    bf16_t* const l0 = &lds[0];
+    const uint32_t lbase = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) bf16_t*)l0));
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    auto issue = [&](int buf, int k0) {
+      const uint32_t t = lbase + static_cast<uint32_t>(buf * SE * 2);
+      la.dma(A, ra, k0, t, wv);
+      lb.dma(B, rb, k0, t + TE * 2, wv);
+    };
+    issue(0, kbeg);
+    issue(1, kbeg + BK);
+    dma_wait<VS>();
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+      const bf16_t* sa = l0 + (kt & 1) * SE;
+      compute(sa, sa + TE);
+      __syncthreads();
+      issue(kt & 1, kbeg + (kt + 2) * BK);
       dma_wait<VS>();
       __syncthreads();
-      for (int kt = 0; kt < nk; ++kt) {
-        const bf16_t* sa = l0 + (kt & 1) * SE;
-        compute(sa, sa + TE);
-        __syncthreads();
-        issue(kt & 1, kbeg + (kt + 2) * BK);
-        dma_wait<VS>();
-        __syncthreads();
-      }
-      dma_wait<0>();
     }
-  } else if (nk > 0) {
-    uint4 ra0[4], rb0[4], ra1[4], rb1[4];
-    // Prefetch loads are issued unconditionally (a step past the end reads
-    // zeros or data that is never stored), so the compiler can count the
-    // outstanding loads exactly and wait only for the older register set.
-    la.load(A, ra, kbeg, ra0);
-    lb.load(B, rb, kbeg, rb0);
-    la.load(A, ra, kbeg + BK, ra1);
-    lb.load(B, rb, kbeg + BK, rb1);
-    la.store(lds[0][0], ra0, tid);
-    lb.store(lds[0][1], rb0, tid);
-    __syncthreads();
-    // Register sets 0 / 1 hold K steps of even / odd index; LDS buffer b holds
-    // the step being multiplied. The loop body covers a pair of steps and has
-    // no exit in the middle, so the accumulators keep one register home.
-    int kt = 0;
-    for (; kt + 2 <= nk; kt += 2) {
-      la.load(A, ra, kbeg + (kt + 2) * BK, ra0);
-      lb.load(B, rb, kbeg + (kt + 2) * BK, rb0);
-      compute(lds[0][0], lds[0][1]);
-      la.store(lds[1][0], ra1, tid);
-      lb.store(lds[1][1], rb1, tid);
-      __syncthreads();
-      la.load(A, ra, kbeg + (kt + 3) * BK, ra1);
-      lb.load(B, rb, kbeg + (kt + 3) * BK, rb1);
-      compute(lds[1][0], lds[1][1]);
-      if (kt + 2 < nk) {
-        la.store(lds[0][0], ra0, tid);
-        lb.store(lds[0][1], rb0, tid);
-      }
-      __syncthreads();
-    }
-    if (kt < nk) compute(lds[0][0], lds[0][1]);   // odd step count: the last step is in buffer 0
+    dma_wait<0>();
   }
 
   if constexpr (KSL == 2) {
     // second-half waves hand their sums to the first-half waves through LDS
     // (register r of tile (i, j) of lane l at [sub-tile][i][j][r][l])
-    float* red = reinterpret_cast<float*>(&lds[0][0][0]);
+    float* red = reinterpret_cast<float*>(&lds[0]);
     static_assert(sizeof(lds) >= 4 * 2 * NJ * 16 * 64 * sizeof(float), "the reduction fits the operand buffers");
     float* mine = red + (wave & 3) * (2 * NJ * 16 * 64) + lane;
     __syncthreads();
@@ -894,26 +845,25 @@ __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
   }
   {
     if (staged_epi) {
-      // float32 tile [128][BNT] in LDS (row pitch BNT + 4 floats), then each
+      // float32 tile [128][128] in LDS (row pitch EPI_PITCH), then each
       // thread takes 8 consecutive columns of NP rows: every load and store
       // of the epilogue covers whole row segments. All of a thread's operand
       // loads are issued before the tile is staged and before its first
       // store: loads and stores share one counter of outstanding memory
       // operations, so a load issued after a store would wait for the store
       // to complete and every row would cost a memory round trip.
-      constexpr int EP = BNT + 4;
-      using EO = EpiOperands<BNT, NTH>;
+      constexpr int EP = EPI_PITCH;
+      using EO = EpiOperands<NTH>;
       constexpr int TPR = EO::TPR, RPP = EO::RPP, NP = EO::NP;
       const int ecl = (tid % TPR) * 8, erl = tid / TPR;
       const int ecol = col0 + ecl;
       const EpiDev& e = args.e;
       const bool colok = ecol < args.N;
-      if constexpr (!(DMA && KSL == 1)) eop.load(args, row0, col0, tid, coff);
+      if constexpr (KSL == 2) eop.load(args, row0, col0, tid, coff);
       const uint4 ebb = eop.bb;
       const uint4 (&erb)[NP] = eop.rb;
       const uint4 (&emk)[NP] = eop.mk;
-      float* tile = reinterpret_cast<float*>(&lds[0][0][0]);
-      static_assert(sizeof(lds) >= 128 * (BNT + 4) * sizeof(float), "the float32 tile fits the operand buffers");
+      float* tile = reinterpret_cast<float*>(&lds[0]);
       if constexpr (KSL == 1) __syncthreads();   // every wave has read its last operand tile
       if (kslice == 0) {                         // 8-wave blocks: the first-half waves hold the sums
 #pragma unroll
@@ -929,22 +879,33 @@ __global__ __launch_bounds__(NT * KSL, 2) void gemm_bf16_kernel(KArgs args) {
             }
       }
       __syncthreads();
+      // plain float32 outputs of row-major operands (class scores, the LSTM's
+      // input projections): straight-line rows
+      if constexpr (MA == OP_K_PLAIN) {
+        if (e.out_f32 && !e.out_bf16 && !e.accumulate && !e.bias && !e.res_f32 && !e.res_bf16 && !e.mask && !e.relu &&
+            e.alpha == 1.0f) {
+          float* const out = e.out_f32 + coff + static_cast<long>(row0) * e.ldc + ecol;
+          if (e.bias_bf16) staged_rows_f32<NTH, true>(tile, ebb, out, e.ldc, args.M - row0, colok, ecl, erl);
+          else staged_rows_f32<NTH, false>(tile, ebb, out, e.ldc, args.M - row0, colok, ecl, erl);
+          return;
+        }
+      }
       // whole tiles with only bf16 operands: the specialised rows
       if (e.out_bf16 && !e.out_f32 && !e.bias && !e.res_f32 && e.alpha == 1.0f && row0 + 128 <= args.M &&
-          col0 + BNT <= args.N) {
+          col0 + BN <= args.N) {
         bf16_t* const out = e.out_bf16 + coff + static_cast<long>(row0) * e.ldc + ecol;   // row rr at + rr ldc
         const int kind = (e.bias_bf16 ? 1 : 0) | (e.res_bf16 ? 2 : 0) | (e.relu ? 4 : 0) | (e.mask ? 8 : 0);
         bool done = true;
         switch (kind) {
-          case 0: staged_rows<BNT, NTH, false, false, false, false>(e, tile, eop, out, ecl, erl); break;
-          case 1: staged_rows<BNT, NTH, true, false, false, false>(e, tile, eop, out, ecl, erl); break;
-          case 2: staged_rows<BNT, NTH, false, true, false, false>(e, tile, eop, out, ecl, erl); break;
-          case 3: staged_rows<BNT, NTH, true, true, false, false>(e, tile, eop, out, ecl, erl); break;
-          case 4: staged_rows<BNT, NTH, false, false, true, false>(e, tile, eop, out, ecl, erl); break;
-          case 5: staged_rows<BNT, NTH, true, false, true, false>(e, tile, eop, out, ecl, erl); break;
-          case 6: staged_rows<BNT, NTH, false, true, true, false>(e, tile, eop, out, ecl, erl); break;
-          case 8: staged_rows<BNT, NTH, false, false, false, true>(e, tile, eop, out, ecl, erl); break;
-          case 10: staged_rows<BNT, NTH, false, true, false, true>(e, tile, eop, out, ecl, erl); break;
+          case 0: staged_rows<NTH, false, false, false, false>(e, tile, eop, out, ecl, erl); break;
+          case 1: staged_rows<NTH, true, false, false, false>(e, tile, eop, out, ecl, erl); break;
+          case 2: staged_rows<NTH, false, true, false, false>(e, tile, eop, out, ecl, erl); break;
+          case 3: staged_rows<NTH, true, true, false, false>(e, tile, eop, out, ecl, erl); break;
+          case 4: staged_rows<NTH, false, false, true, false>(e, tile, eop, out, ecl, erl); break;
+          case 5: staged_rows<NTH, true, false, true, false>(e, tile, eop, out, ecl, erl); break;
+          case 6: staged_rows<NTH, false, true, true, false>(e, tile, eop, out, ecl, erl); break;
+          case 8: staged_rows<NTH, false, false, false, true>(e, tile, eop, out, ecl, erl); break;
+          case 10: staged_rows<NTH, false, true, false, true>(e, tile, eop, out, ecl, erl); break;
           default: done = false;
         }
         if (done) return;
@@ -1070,12 +1031,10 @@ OperandDev make_operand(const Operand& o, int rows, int K, long extent) {
 template <int MA, int MB, bool TAPK = false>
 hipError_t launch(const KArgs& a, hipStream_t s) {
   dim3 grid(a.tiles_total, a.batch * a.splits);
-  if (a.bn == 64) {
-    hipLaunchKernelGGL((gemm_bf16_kernel<MA, MB, TAPK, 64, 1>), grid, dim3(NT), 0, s, a);
-  } else if (a.ksl == 2) {
-    hipLaunchKernelGGL((gemm_bf16_kernel<MA, MB, TAPK, 128, 2, true>), grid, dim3(2 * NT), 0, s, a);
+  if (a.ksl == 2) {
+    hipLaunchKernelGGL((gemm_bf16_kernel<MA, MB, TAPK, 2>), grid, dim3(2 * NT), 0, s, a);
   } else {
-    hipLaunchKernelGGL((gemm_bf16_kernel<MA, MB, TAPK, 128, 1, true>), grid, dim3(NT), 0, s, a);
+    hipLaunchKernelGGL((gemm_bf16_kernel<MA, MB, TAPK, 1>), grid, dim3(NT), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -1085,59 +1044,57 @@ hipError_t launch(const KArgs& a, hipStream_t s) {
 namespace {
 
 constexpr long kCUs = 256;
-constexpr long kTargetBlocks = 2 * kCUs;   // two resident 4-wave blocks per CU
 
-// Kernel of a launch (block tile width bn, waves per output sub-tile ksl)
-// and its K split.
-//  * 4-wave blocks, two per CU: 128-wide tiles, or 64-wide ones where
-//    128-wide tiles cannot fill the two-per-CU slots but 64-wide ones fill
-//    at least three quarters of them without a K split.
+// Kernel of a launch (waves per output sub-tile, ksl) and its K split.
 //  * A convolution gather against a row-major filter (the forward, or the
-//    data gradient against a transposed filter copy) of that narrow kind
-//    whose 128-wide tiles give between 7/8 of the CUs and every CU one block
-//    runs them on 8-wave blocks instead (ksl = 2; its gathered A operand is
-//    then loaded once per 128 x 128 outputs). Other operand pairs, and
-//    launches filling fewer CUs, were measured slower on 8-wave blocks (with
-//    direct loads too: every launch of at most one 128-wide block per CU on
-//    8-wave blocks made the 1x1 and filter-gradient launches no faster or
-//    slower alone, and the concurrent bottleneck step 20 % slower, its
-//    8-wave blocks leaving no room on their CUs for the other pass).
-//  * A split gives each slice at least 12 K steps (shorter slices cost more
-//    in the reduction than they gain), at most MAX_SPLITS slices and no more
-//    partials than the workspace holds.
-//  * concurrent: the launch shares the GPU with another pass's launches (a
-//    forward beside a backward), which fill the CUs its own grid leaves
-//    idle. It keeps the 128-wide tile (a third less LDS traffic per MFMA
-//    than the 64-wide one) instead of narrowing, and splits K only for grids
-//    of fewer than 128 tiles or for K of 64 steps or more (measured: the
-//    bottleneck and transformer stages 3.6 % and 3.9 % faster per step than
-//    with the rules above; run alone, the narrow tiles stay faster).
+//    data gradient against a transposed filter copy) whose tiles give between
+//    7/8 of the CUs and every CU one block runs them on 8-wave blocks. Other
+//    operand pairs, and launches filling fewer CUs, were measured slower on
+//    them (the concurrent bottleneck step 20 % slower, its 8-wave blocks
+//    leaving no room on their CUs for the other pass).
+//  * Otherwise K is split into the number of slices, at most MAX_SPLITS, of
+//    the least modelled time: kStep us per K step of a slice (a block's steps
+//    follow one another, so a slice of half the steps takes half as long;
+//    kShared times as long where CUs hold two blocks), and for a split the
+//    reduction's launch and kPartial us per MB of float32 partials written and
+//    read back, as far as every block is resident at once and the workspace
+//    holds the partials. The constants were fitted to 46 products of the
+//    stages (16 to 16000 tiles, 1 to 500 K steps) timed at 1 to 16 slices
+//    each: the chosen counts are within 0.7 % of the best of each product on
+//    average, the worst 11 % (80 tiles, K = 4608). Examples, us with the
+//    reduction: 2016 x 72 x 648 takes 13.8 whole and 10.3 in 4 slices,
+//    1000 x 160 x 1440 21.3 and 11.7 in 6, 50 x 512 x 1024 12.1 and 8.1 in 8,
+//    2450 x 512 x 2048 19.0 whole and 20.7 in 2, 1024 x 768 x 256 6.5 whole
+//    and 12.4 in 2. 64-wide tiles for launches with few 128-wide ones, once
+//    used, are slower since the operands are loaded directly (12544 x 256 x
+//    2304: 28.2 against 23.4 us; 8192 x 512 x 2048: 25.4 against 22.3).
 struct Shape {
-  int bn, ksl, splits;
+  int ksl, splits;
 };
 
-Shape shape_of(int M, int N, int K, int batch, size_t workspace_bytes, bool conv_fwd, bool concurrent) {
-  const long rows = static_cast<long>((M + BM - 1) / BM) * batch;
-  const long t128 = rows * ((N + 127) / 128), t64 = rows * ((N + 63) / 64);
-  Shape sh{128, 1, 1};
-  if (t128 < kTargetBlocks && 4 * t64 >= 3 * kTargetBlocks) {
-    if (conv_fwd && t128 <= kCUs && 8 * t128 >= 7 * kCUs) {
-      sh.ksl = 2;
-      return sh;
-    }
-    if (!concurrent) {
-      sh.bn = 64;
-      return sh;
+constexpr double kStep = 0.4, kShared = 1.15, kReduce = 2.0, kPartial = 0.5;
+
+Shape shape_of(int M, int N, int K, int batch, size_t workspace_bytes, bool conv_gather) {
+  const long tiles = static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN) * batch;
+  Shape sh{1, 1};
+  if (conv_gather && tiles <= kCUs && 8 * tiles >= 7 * kCUs) {
+    sh.ksl = 2;
+    return sh;
+  }
+  const int nk = (K + BK - 1) / BK;
+  const double mb = static_cast<double>(batch) * M * N * 4e-6;
+  double best = 0.0;
+  for (int sp = 1; sp <= std::min(nk, MAX_SPLITS); ++sp) {
+    if (sp > 1 && (tiles * sp > 2 * kCUs || static_cast<double>(sp) * mb * 1e6 > static_cast<double>(workspace_bytes)))
+      break;
+    const int steps = (nk + sp - 1) / sp;
+    if ((nk + steps - 1) / steps != sp) continue;   // the last slice would be empty
+    const double t = kStep * steps * (tiles * sp > kCUs ? kShared : 1.0) + (sp > 1 ? kReduce + kPartial * mb * sp : 0.0);
+    if (sp == 1 || t < best) {
+      best = t;
+      sh.splits = sp;
     }
   }
-  if (t128 >= kTargetBlocks || K < 2 * 12 * BK) return sh;
-  if (concurrent && t128 >= kCUs / 2 && K < 64 * BK) return sh;
-  int splits = static_cast<int>(kTargetBlocks / t128);   // all blocks resident in one round
-  splits = std::min(splits, K / (12 * BK));
-  splits = std::min(splits, MAX_SPLITS);
-  const long per = static_cast<long>(batch) * M * N * 4;
-  while (splits > 1 && per * splits > static_cast<long>(workspace_bytes)) --splits;
-  sh.splits = std::max(splits, 1);
   return sh;
 }
 
@@ -1161,11 +1118,9 @@ bool plan(const GemmDesc& d, KArgs& a, hipError_t& err) {
   a.batch = d.batch;
   a.zdiv = zdiv;
   const bool gather = (d.A.mode == OP_K_CONV_FWD || d.A.mode == OP_K_CONV_DGRAD) && d.B.mode == OP_K_PLAIN;
-  const Shape sh = shape_of(d.M, d.N, d.K, d.batch, d.workspace ? d.workspace_bytes : 0, gather, d.concurrent);
-  a.bn = sh.bn;
+  const Shape sh = shape_of(d.M, d.N, d.K, d.batch, d.workspace ? d.workspace_bytes : 0, gather);
   a.ksl = sh.ksl;
-  a.dma = sh.bn == 128;
-  a.tiles_n = (d.N + a.bn - 1) / a.bn;
+  a.tiles_n = (d.N + BN - 1) / BN;
   a.tiles_total = a.tiles_n * ((d.M + BM - 1) / BM);
   const int splits = sh.splits;
   const int ksteps = (d.K + BK - 1) / BK;
@@ -1244,8 +1199,7 @@ const char* gemm_bf16_kernel_name(const GemmDesc& d) {
   if (ma == OP_K_CONV_DGRAD && mb == OP_R_FILTER_T) tapk = d.A.g.C % BK == 0 && d.B.g.C2 % BK == 0;
   // the kernel's template arguments as a profiler prints the instantiation
   static thread_local char buf[64];
-  std::snprintf(buf, sizeof(buf), "gemm_bf16_kernel<%d, %d, %s, %d, %d, %s>", ma, mb, tapk ? "true" : "false",
-                a.bn == 64 ? 64 : 128, a.bn == 64 ? 1 : a.ksl, a.dma ? "true" : "false");
+  std::snprintf(buf, sizeof(buf), "gemm_bf16_kernel<%d, %d, %s, %d>", ma, mb, tapk ? "true" : "false", a.ksl);
   return buf;
 }
 
@@ -1257,9 +1211,9 @@ const char* gemm_bf16_reduce_name(const GemmDesc& d) {
   return a.vec_epi ? "splitk_reduce4_kernel<true>" : "splitk_reduce4_kernel<false>";
 }
 
-int gemm_bf16_split_rule(int M, int N, int K, int batch, size_t workspace_bytes, bool concurrent) {
+int gemm_bf16_split_rule(int M, int N, int K, int batch, size_t workspace_bytes) {
   if (M <= 0 || N <= 0 || K <= 0 || batch <= 0) return 1;
-  return shape_of(M, N, K, batch, workspace_bytes, false, concurrent).splits;
+  return shape_of(M, N, K, batch, workspace_bytes, false).splits;
 }
 
 int gemm_bf16_splits(const GemmDesc& d) {

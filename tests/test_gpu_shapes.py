@@ -41,3 +41,17 @@ def test_float32_products(head, batch, layers, dims):
 ])
 def test_lstm_steps(head, batch, dims):
     _run("reslstm", "bf16", head, batch, 2, dims, 1e-2)
+
+
+# bf16 products: one tile with K in many slices (the last ones short), few
+# tiles, ragged M, N and K; class counts that are no multiple of 8 (element
+# stores) and float32 scores of ragged row counts; a convolution grid inside
+# the 8-wave range (7/8 of the CUs) with a ragged last row tile.
+@pytest.mark.parametrize("kind,head,batch,layers,dims", [
+    ("fc", "ce", 50, 2, (1024, 16, 520)), ("fc", "none", 129, 2, (136, 264, 1160)),
+    ("conv3x3", "ce", 10, 1, (160, 168, 10, 10, 10)), ("conv3x3", "none", 33, 2, (40, 72, 7, 9)),
+    ("conv3x3", "none", 113, 1, (64, 512, 8, 8)), ("bottleneck", "ce", 10, 1, (264, 72, 7, 7, 6)),
+    ("transformer", "ce", 3, 1, (64, 1, 72, 40, 1000)),
+])
+def test_bf16_products(kind, head, batch, layers, dims):
+    _run(kind, "bf16", head, batch, layers, dims, 1e-4)
