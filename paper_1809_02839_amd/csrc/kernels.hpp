@@ -124,12 +124,21 @@ hipError_t transpose_bf16(const bf16_t* X, int R, int C, bf16_t* Y, hipStream_t 
 // block per batch x head), on the packed qkv [B*S][3d] of a layer. Forward
 // writes ctx [B*S][d] and the softmax row statistics (max, 1/sum) as float32
 // [B*heads*S][2]; backward recomputes P from them and writes dQ, dK, dV into
-// dqkv [B*S][3d]. Other shapes use the batched GEMM path.
+// dqkv [B*S][3d]. Other shapes use attention_long or the batched GEMM path.
 bool attention_fused_supported(int seq, int head_dim, int d);
 hipError_t attention_fwd(const bf16_t* qkv, int batch, int heads, int d, float scale, float* stats, bf16_t* ctx,
                          hipStream_t s);
 hipError_t attention_bwd(const bf16_t* qkv, const bf16_t* dctx, const float* stats, int batch, int heads, int d,
                          float scale, bf16_t* dqkv, hipStream_t s);
+
+// The same for any sequence length (a multiple of 8) at head dimension 32 or
+// 64, 128 x 128 score tiles recomputed on chip in both passes. dots: B*heads*S
+// floats of workspace.
+bool attention_long_supported(int batch, int heads, int head_dim);
+hipError_t attention_long_fwd(const bf16_t* qkv, int batch, int S, int heads, int d, float scale, float* stats,
+                              bf16_t* ctx, hipStream_t s);
+hipError_t attention_long_bwd(const bf16_t* qkv, const bf16_t* dctx, const float* stats, int batch, int S, int heads,
+                              int d, float scale, float* dots, bf16_t* dqkv, hipStream_t s);
 
 // Row chunking of the two-pass column reductions (column sums, layer-norm
 // parameter gradients) and the float32 workspace each pass needs.

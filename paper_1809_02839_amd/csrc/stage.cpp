@@ -498,11 +498,11 @@ void Stage::plan_buffers() {
       const long d = dm[0], H = dm[1], F = dm[2], S = dm[3], T = B * S;
       const bool ce = d_.head == SPECTRAIN_HEAD_CE;
       const long V = ce ? dm[4] : 0;
-      const bool fused = attention_fused_supported(static_cast<int>(S), static_cast<int>(d / H), static_cast<int>(d));
-      // the fused attention keeps only softmax row statistics; the GEMM path P (f32, bf16) and the scores
-      const long BHSS = fused ? 0 : B * H * S * S;
+      const Attention core = attention();
+      // the fused cores keep only softmax row statistics; the GEMM path P (f32, bf16) and the scores
+      const long BHSS = core == Attention::kGemm ? B * H * S * S : 0;
       for (int l = 0; l < L; ++l) {
-        size_t s[13] = {static_cast<size_t>(T * 3 * d * 2), static_cast<size_t>(fused ? B * H * S * 2 * 4 : BHSS * 4),
+        size_t s[13] = {static_cast<size_t>(T * 3 * d * 2), static_cast<size_t>(BHSS ? BHSS * 4 : B * H * S * 2 * 4),
                         static_cast<size_t>(BHSS * 2),      static_cast<size_t>(T * d * 2),
                         static_cast<size_t>(T * d * 2),     static_cast<size_t>(T * 4),
                         static_cast<size_t>(T * 4),         static_cast<size_t>(T * d * 2),
@@ -512,7 +512,7 @@ void Stage::plan_buffers() {
         st.insert(st.end(), s, s + 13);
       }
       st.push_back(ce ? T * V * 2 : 0);   // dlogits (bf16) at id 13 L
-      ws = {static_cast<size_t>(BHSS * 4), static_cast<size_t>(BHSS * 2), static_cast<size_t>(T * d * 2),
+      ws = {static_cast<size_t>(BHSS ? BHSS * 4 : B * H * S * 4), static_cast<size_t>(BHSS * 2), static_cast<size_t>(T * d * 2),
             static_cast<size_t>(T * d * 2), static_cast<size_t>(T * d * 2), static_cast<size_t>(T * F * 2),
             static_cast<size_t>(T * d * 2), static_cast<size_t>(T * d * 2), static_cast<size_t>(T * d * 2),
             static_cast<size_t>(T * 3 * d * 2), static_cast<size_t>(ce ? T * V * 4 : 0),
@@ -556,6 +556,14 @@ void Stage::plan_buffers() {
   }
   DeviceBlock probe;
   stash_bytes_ = st;
+  if (d_.kind == SPECTRAIN_KIND_TRANSFORMER && attention() == Attention::kTiles) {
+    // read_stash hands out the probabilities, recomputed, under their ids
+    const size_t scores = static_cast<size_t>(B) * dm[1] * dm[3] * dm[3];
+    for (int l = 0; l < L; ++l) {
+      stash_bytes_[13 * l + 1] = scores * 4;
+      stash_bytes_[13 * l + 2] = scores * 2;
+    }
+  }
   for (size_t b : st) stash_off_.push_back(probe.add(std::max<size_t>(b, 1)));
   for (size_t b : ws) ws_off_.push_back(ws_block_.add(std::max<size_t>(b, 1)));
   // a second copy for a forward that runs beside a backward (the combined
@@ -763,6 +771,17 @@ size_t Stage::read_stash(int64_t mb, int index, void* host, size_t capacity) {
   if (capacity < n) fail("host buffer of " + std::to_string(capacity) + " bytes is smaller than the stash buffer (" +
                          std::to_string(n) + " bytes)");
   sync();
+  if (d_.kind == SPECTRAIN_KIND_TRANSFORMER && attention() == Attention::kTiles && index < 13 * d_.num_layers &&
+      (index % 13 == 1 || index % 13 == 2)) {
+    const size_t count = stash_bytes_[index - index % 13 + 2] / 2;
+    DeviceBlock tmp;
+    const size_t os = tmp.add(count * 4), op = tmp.add(count * 4), ob = tmp.add(count * 2);
+    tmp.allocate();
+    attention_probs(stash<bf16_t>(slot, index - index % 13), tmp.at<float>(os), tmp.at<float>(op), tmp.at<bf16_t>(ob));
+    sync();
+    hip_check(hipMemcpy(host, tmp.at<char>(index % 13 == 1 ? op : ob), n, hipMemcpyDeviceToHost), "copy stash");
+    return n;
+  }
   hip_check(hipMemcpy(host, slot_blocks_[slot].at<char>(stash_off_[index]), n, hipMemcpyDeviceToHost), "copy stash");
   return n;
 }
@@ -1171,9 +1190,32 @@ void Stage::bwd_bneck(int slot, const void* dy, void* dx) {
 }
 
 // ======================================================= TRANSFORMER ====
+Stage::Attention Stage::attention() const {
+  const int B = d_.batch, d = d_.dims[0], Hh = d_.dims[1], S = d_.dims[3];
+  if (attention_fused_supported(S, d / Hh, d)) return Attention::kBlock;
+  return attention_long_supported(B, Hh, d / Hh) ? Attention::kTiles : Attention::kGemm;
+}
+
+void Stage::attention_probs(const bf16_t* qkv, float* scores, float* P, bf16_t* Pb) {
+  const int B = d_.batch, d = d_.dims[0], Hh = d_.dims[1], S = d_.dims[3], dh = d / Hh;
+  // scores[b, h] = Q K^T * scale
+  Operand qa = opK(qkv, 3 * d), kb = opK(qkv + d, 3 * d);
+  qa.bs1 = kb.bs1 = static_cast<long>(S) * 3 * d;
+  qa.bs2 = kb.bs2 = dh;
+  GemmDesc sc = gd(S, S, dh, qa, kb, S);
+  sc.batch = B * Hh;
+  sc.zdiv = Hh;
+  sc.epi.bs1 = static_cast<long>(Hh) * S * S;
+  sc.epi.bs2 = static_cast<long>(S) * S;
+  sc.epi.alpha = 1.0f / std::sqrt(static_cast<float>(dh));
+  sc.epi.out_f32 = scores;
+  gemm(sc);
+  LAUNCH("softmax", 0, 10.0 * B * Hh * S * S, softmax_rows(scores, B * Hh * S, S, P, Pb, ls_));
+}
+
 // Post-LN encoder layer; per layer stash ids 13*l + j:
-// 0 qkv, 1 P (f32; with the fused attention core the softmax row statistics),
-// 2 P (bf16; unused with the fused core), 3 ctx, 4 r1, 5 mean1, 6 rstd1, 7 h,
+// 0 qkv, 1 P (f32; with the fused attention cores the softmax row statistics),
+// 2 P (bf16; unused with the fused cores), 3 ctx, 4 r1, 5 mean1, 6 rstd1, 7 h,
 // 8 f1, 9 r2, 10 mean2, 11 rstd2, 12 layer output (l < L-1, or every layer
 // with a CE head); id 13 L: dlogits (bf16) with a CE head.
 void Stage::fwd_tfm(int slot, const void* x, void* y, const int32_t* labels, float* loss) {
@@ -1181,6 +1223,7 @@ void Stage::fwd_tfm(int slot, const void* x, void* y, const int32_t* labels, flo
   const int T = B * S, dh = d / Hh;
   const bool ce = d_.head == SPECTRAIN_HEAD_CE;
   const float scale = 1.0f / std::sqrt(static_cast<float>(dh));
+  const Attention core = attention();
   const void* a = x;
   for (int l = 0; l < L; ++l) {
     const int p = 12 * l, q = 13 * l;
@@ -1198,23 +1241,14 @@ void Stage::fwd_tfm(int slot, const void* x, void* y, const int32_t* labels, flo
     g.epi.bias_bf16 = static_cast<const bf16_t*>(wf(p + 1));
     g.epi.out_bf16 = qkv;
     gemm(g);
-    if (attention_fused_supported(S, dh, d)) {
+    if (core == Attention::kTiles) {
+      LAUNCH("attention_long", 4.0 * B * Hh * S * S * dh, 2.0 * T * 4 * d + 8.0 * B * Hh * S,
+             attention_long_fwd(qkv, B, S, Hh, d, scale, P, ctx, ls_));
+    } else if (core == Attention::kBlock) {
       LAUNCH("attention", 4.0 * B * Hh * S * S * dh, 2.0 * T * 4 * d + 8.0 * B * Hh * S,
              attention_fwd(qkv, B, Hh, d, scale, P, ctx, ls_));
     } else {
-    // scores[b, h] = Q K^T * scale
-    Operand qa = opK(qkv, 3 * d), kb = opK(qkv + d, 3 * d);
-    qa.bs1 = kb.bs1 = static_cast<long>(S) * 3 * d;
-    qa.bs2 = kb.bs2 = dh;
-    GemmDesc sc = gd(S, S, dh, qa, kb, S);
-    sc.batch = B * Hh;
-    sc.zdiv = Hh;
-    sc.epi.bs1 = static_cast<long>(Hh) * S * S;
-    sc.epi.bs2 = static_cast<long>(S) * S;
-    sc.epi.alpha = scale;
-    sc.epi.out_f32 = ws<float>(0);
-    gemm(sc);
-    LAUNCH("softmax", 0, 10.0 * B * Hh * S * S, softmax_rows(ws<float>(0), B * Hh * S, S, P, Pb, ls_));
+    attention_probs(qkv, ws<float>(0), P, Pb);
     // ctx[b, :, h] = P V
     Operand pa = opK(Pb, S), vb = opR(qkv + 2 * d, 3 * d);
     pa.bs1 = static_cast<long>(Hh) * S * S;
@@ -1262,13 +1296,14 @@ void Stage::fwd_tfm(int slot, const void* x, void* y, const int32_t* labels, flo
   }
 }
 
-// workspace ids: 0 scores/dP (f32), 1 dS, 2/3 layer-output gradient ping-pong,
+// workspace ids: 0 scores/dP (f32; kTiles: row sums of P dP), 1 dS, 2/3 layer-output gradient ping-pong,
 // 4 dr2, 5 df1, 6 dh, 7 dr1, 8 dctx, 9 dqkv, 10 logits (f32, CE head),
 // 11 per-token losses (CE head), 12 column-sum partials
 void Stage::bwd_tfm(int slot, const void* dy, void* dx) {
   const int L = d_.num_layers, B = d_.batch, d = d_.dims[0], Hh = d_.dims[1], F = d_.dims[2], S = d_.dims[3];
   const int T = B * S, dh = d / Hh;
   const float scale = 1.0f / std::sqrt(static_cast<float>(dh));
+  const Attention core = attention();
   const Slot& sl = slots_[slot];
   float* part = ws<float>(ws_colsum_);
   float* part2 = ws<float>(ws_colsum2_);
@@ -1354,7 +1389,10 @@ void Stage::bwd_tfm(int slot, const void* dy, void* dx) {
 
     // attention backward: fused, or batched GEMMs over (b, h)
     protect(dqkv);
-    if (attention_fused_supported(S, dh, d)) {
+    if (core == Attention::kTiles) {
+      LAUNCH("attention_long_bwd", 10.0 * B * Hh * S * S * dh, 2.0 * T * 7 * d + 8.0 * B * Hh * S,
+             attention_long_bwd(qkv, dctx, P, B, S, Hh, d, scale, ws<float>(0), dqkv, s_));
+    } else if (core == Attention::kBlock) {
       LAUNCH("attention_bwd", 10.0 * B * Hh * S * S * dh, 2.0 * T * 7 * d + 8.0 * B * Hh * S,
              attention_bwd(qkv, dctx, P, B, Hh, d, scale, dqkv, s_));
     } else {

@@ -227,6 +227,13 @@ class Stage {
                      const int32_t* labels, float* loss);
   void pool_head_bwd(int slot, const void* yl, int HW, int C, int t, int id_pool, int id_dl, int wsl, void* dz);
   void bwd_bneck(int slot, const void* dy, void* dx);
+  // Which attention core the stage's shape takes: one block per head (S = 128),
+  // tiles recomputed on chip, or batched GEMMs with stored probabilities.
+  enum class Attention { kBlock, kTiles, kGemm };
+  Attention attention() const;
+  // Softmax probabilities of every head from a layer's qkv by the batched
+  // GEMM: scores (workspace, float32) -> P and bf16(P).
+  void attention_probs(const bf16_t* qkv, float* scores, float* P, bf16_t* Pb);
   void fwd_tfm(int slot, const void* x, void* y, const int32_t* labels, float* loss);
   void bwd_tfm(int slot, const void* dy, void* dx);
   void fwd_lstm(int slot, const void* x, void* y, const int32_t* labels, float* loss);

@@ -55,3 +55,41 @@ def test_lstm_steps(head, batch, dims):
 ])
 def test_bf16_products(kind, head, batch, layers, dims):
     _run(kind, "bf16", head, batch, layers, dims, 1e-4)
+
+
+# dims (d, heads, ffn, S[, vocab]): one short score tile, one whole tile at head
+# dimension 32, one row past a tile, whole tiles, and a head dimension that
+# keeps the batched-GEMM form.
+@pytest.mark.parametrize("batch,dims", [
+    (2, (64, 1, 72, 8, 8)), (2, (64, 2, 72, 128, 8)), (3, (128, 2, 136, 136, 8)), (1, (128, 4, 136, 256, 8)),
+    (2, (128, 2, 136, 328, 8)), (2, (64, 4, 72, 48, 8)),
+])
+def test_attention_lengths(batch, dims):
+    _run("transformer", "bf16", "none", batch, 1, dims, 1e-3)
+
+
+@pytest.mark.parametrize("dims", [(64, 2, 72, 136), (128, 2, 136, 40)])
+def test_stash_probabilities(dims):
+    """read_stash ids 1 and 2 hold the softmax probabilities of the stashed
+    qkv. Bounds: float32 scores of up to 64 products and the exponential's own
+    error, 2e-5 of the largest probability; bf16 rounding, 2^-8 of each."""
+    import numpy as np
+
+    from paper_1809_02839_amd import native
+    d, heads, _, S = dims
+    B, dh = 2, d // heads
+    spec = synth.StageSpec("transformer", "bf16", "none", 0, 1, B, 1, dims, 1e-3, 0.9)
+    st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
+    x = torch.from_numpy(synth.stage_input(spec, 0) * 50).cuda().bfloat16()
+    y = torch.empty_like(x)
+    st.forward(0, x, y)
+    raw = {i: st.read_stash(0, i) for i in (0, 1, 2)}
+    bf = lambda a: (a.view(np.uint16).astype(np.uint32) << 16).view(np.float32).astype(np.float64)  # noqa: E731
+    q, k, _ = bf(raw[0]).reshape(B, S, 3, heads, dh).transpose(2, 0, 3, 1, 4)
+    z = q @ k.transpose(0, 1, 3, 2) / np.sqrt(dh)
+    p = np.exp(z - z.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    got = raw[1].view(np.float32).reshape(p.shape)
+    assert np.max(np.abs(got - p)) <= 2e-5 * p.max()
+    assert np.max(np.abs(bf(raw[2]).reshape(p.shape) - got) / got) <= 2.0 ** -8
+    st.destroy()
