@@ -205,13 +205,15 @@ __global__ __launch_bounds__(NT, 3) void attention_long_fwd_kernel(const bf16_t*
         if (k0 + c0 + col_of(r, lane) < S) t = fmaxf(t, acc[r]);
       }
       t = fmaxf(t, __shfl_xor(t, 32));
+      // scores of -infinity only so far count zero, as against any later maximum
+      const float t0 = t == -INFINITY ? 0.0f : t;
       float e = 0.0f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float x = exp_neg(__fsub_rn(acc[r], t));
+        const float x = exp_neg(__fsub_rn(acc[r], t0));
         e += k0 + c0 + col_of(r, lane) < S ? x : 0.0f;
       }
-      sum = k0 + c0 == 0 ? e : fmaf(sum, exp_neg(__fsub_rn(m, t)), e);
+      sum = k0 + c0 == 0 ? e : fmaf(sum, exp_neg(__fsub_rn(m, t0)), e);
       m = t;
     }
   }

@@ -93,3 +93,32 @@ def test_stash_probabilities(dims):
     assert np.max(np.abs(got - p)) <= 2e-5 * p.max()
     assert np.max(np.abs(bf(raw[2]).reshape(p.shape) - got) / got) <= 2.0 ** -8
     st.destroy()
+
+
+@pytest.mark.parametrize("S,hidden", [(40, 32), (136, 32), (136, 131)])
+def test_scores_of_minus_infinity(S, hidden):
+    """Scores that overflow to -infinity over the first `hidden` keys (whole
+    column groups, a whole tile) weigh nothing: the context is the mean of the
+    other keys' values. bf16 rounding of P, of v and of the result: 3 x 2^-8
+    of the values' mean magnitude."""
+    import numpy as np
+
+    from paper_1809_02839_amd import native
+    d, B = 64, 1
+    spec = synth.StageSpec("transformer", "bf16", "none", 0, 1, B, 1, (d, 1, 72, S), 1e-3, 0.9)
+    W = synth.initial_params(spec)
+    w, b = np.zeros((3 * d, d), np.float32), np.zeros(3 * d, np.float32)
+    b[0] = 1e20                  # q = (1e20, 0, ...)
+    w[d, 0] = -3e20              # k = (-3e20 x0, 0, ...)
+    w[2 * d + 1, 1] = 1.0        # v = (0, x1, 0, ...)
+    W[:w.size], W[w.size:w.size + b.size] = w.ravel(), b
+    x = torch.zeros(B, S, d)
+    x[:, :hidden, 0] = 1.0
+    x[:, :, 1] = 1.0 + torch.arange(S) % 7
+    st = native.Stage(native.desc_from_spec(spec), W, torch.cuda.current_stream())
+    xg = x.cuda().bfloat16()
+    st.forward(0, xg, torch.empty_like(xg))
+    ctx = (st.read_stash(0, 3).view(np.uint16).astype(np.uint32) << 16).view(np.float32).reshape(B, S, d)
+    st.destroy()
+    mean = float(x[0, hidden:, 1].mean())
+    assert np.max(np.abs(ctx[..., 1] - mean)) <= 3 * 2.0 ** -8 * mean
