@@ -1082,11 +1082,12 @@ Shape shape_of(int M, int N, int K, int batch, size_t workspace_bytes, bool conv
     return sh;
   }
   const int nk = (K + BK - 1) / BK;
-  const double mb = static_cast<double>(batch) * M * N * 4e-6;
+  // in whole bytes: a workspace of exactly the chosen slices must give the same count again
+  const size_t plane = static_cast<size_t>(batch) * M * N * 4;
+  const double mb = plane * 1e-6;
   double best = 0.0;
   for (int sp = 1; sp <= std::min(nk, MAX_SPLITS); ++sp) {
-    if (sp > 1 && (tiles * sp > 2 * kCUs || static_cast<double>(sp) * mb * 1e6 > static_cast<double>(workspace_bytes)))
-      break;
+    if (sp > 1 && (tiles * sp > 2 * kCUs || sp * plane > workspace_bytes)) break;
     const int steps = (nk + sp - 1) / sp;
     if ((nk + steps - 1) / steps != sp) continue;   // the last slice would be empty
     const double t = kStep * steps * (tiles * sp > kCUs ? kShared : 1.0) + (sp > 1 ? kReduce + kPartial * mb * sp : 0.0);
@@ -1122,8 +1123,13 @@ bool plan(const GemmDesc& d, KArgs& a, hipError_t& err) {
   a.ksl = sh.ksl;
   a.tiles_n = (d.N + BN - 1) / BN;
   a.tiles_total = a.tiles_n * ((d.M + BM - 1) / BM);
-  const int splits = sh.splits;
+  const int splits = d.splits > 0 ? d.splits : sh.splits;
   const int ksteps = (d.K + BK - 1) / BK;
+  if (d.splits > 0 && (sh.ksl != 1 || splits > MAX_SPLITS ||
+                       (splits > 1 && (!d.workspace || splits * (static_cast<size_t>(d.batch) * d.M * d.N * 4) > d.workspace_bytes)))) {
+    err = hipErrorInvalidValue;
+    return false;
+  }
   a.k_per_split = ((ksteps + splits - 1) / splits) * BK;
   a.splits = splits;
   a.partial = d.workspace;

@@ -56,6 +56,7 @@ struct GemmDesc {
   int batch = 1, zdiv = 1;
   float* workspace = nullptr;      // split-K partials (bf16 GEMM); NULL disables splitting
   size_t workspace_bytes = 0;
+  int splits = 0;                  // K slices fixed by the caller (bf16 GEMM; they fit the workspace), 0: by rule
   Operand A, B;
   Epilogue epi;
 };

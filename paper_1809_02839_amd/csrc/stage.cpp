@@ -346,6 +346,7 @@ void Stage::gemm(const GemmDesc& d, bool defer) {
         defer_used_ + splits * mn <= defer_cap_ && defer_segs_.size() < static_cast<size_t>(UPDATE_MAX_SEGMENTS)) {
       dd.workspace = defer_ + defer_used_;
       dd.workspace_bytes = static_cast<size_t>(splits * mn) * 4;
+      dd.splits = splits;   // the update sums this many planes: settled here once
       // the partial planes replace the g write: splits - 1 planes more
       LAUNCH_X(prof_on_ ? gemm_bf16_kernel_name(dd) : "gemm_bf16", flops, bytes, 4.0 * (splits - 1) * mn,
                gemm_bf16(dd, ls_, GEMM_MAIN));

@@ -122,3 +122,16 @@ def test_scores_of_minus_infinity(S, hidden):
     st.destroy()
     mean = float(x[0, hidden:, 1].mean())
     assert np.max(np.abs(ctx[..., 1] - mean)) <= 3 * 2.0 ** -8 * mean
+
+
+# Filter gradients left in K-slice planes for the update: 11 and 3 slices by
+# the rule at these pixel counts. The planes lie in memory that held NaN before,
+# so one that the launch did not write shows.
+@pytest.mark.parametrize("batch,dims", [(32, (128, 128, 14, 14)), (11, (104, 328, 12, 7))])
+def test_filter_gradient_planes(batch, dims):
+    torch.cuda.empty_cache()
+    dirty = torch.full((1 << 28,), float("nan"), device="cuda")
+    torch.cuda.synchronize()
+    del dirty
+    torch.cuda.empty_cache()
+    _run("conv3x3", "bf16", "none", batch, 1, dims, 1e-4)
