@@ -1052,33 +1052,58 @@ constexpr long kCUs = 256;
 //    operand pairs, and launches filling fewer CUs, were measured slower on
 //    them (the concurrent bottleneck step 20 % slower, its 8-wave blocks
 //    leaving no room on their CUs for the other pass).
-//  * Otherwise K is split into the number of slices, at most MAX_SPLITS, of
+//  * SPLIT_TIMED: K is split into the number of slices, at most MAX_SPLITS, of
 //    the least modelled time: kStep us per K step of a slice (a block's steps
 //    follow one another, so a slice of half the steps takes half as long;
 //    kShared times as long where CUs hold two blocks), and for a split the
 //    reduction's launch and kPartial us per MB of float32 partials written and
 //    read back, as far as every block is resident at once and the workspace
-//    holds the partials. The constants were fitted to 46 products of the
-//    stages (16 to 16000 tiles, 1 to 500 K steps) timed at 1 to 16 slices
-//    each: the chosen counts are within 0.7 % of the best of each product on
-//    average, the worst 11 % (80 tiles, K = 4608). Examples, us with the
-//    reduction: 2016 x 72 x 648 takes 13.8 whole and 10.3 in 4 slices,
-//    1000 x 160 x 1440 21.3 and 11.7 in 6, 50 x 512 x 1024 12.1 and 8.1 in 8,
-//    2450 x 512 x 2048 19.0 whole and 20.7 in 2, 1024 x 768 x 256 6.5 whole
-//    and 12.4 in 2. 64-wide tiles for launches with few 128-wide ones, once
-//    used, are slower since the operands are loaded directly (12544 x 256 x
-//    2304: 28.2 against 23.4 us; 8192 x 512 x 2048: 25.4 against 22.3).
+//    holds the partials. The constants were fitted to products of the stages
+//    timed at 1 to 16 slices each. Examples, us with the reduction: 2016 x 72 x
+//    648 takes 13.8 whole and 10.3 in 4 slices, 1000 x 160 x 1440 21.3 and 11.7
+//    in 6, 50 x 512 x 1024 12.1 and 8.1 in 8, 2450 x 512 x 2048 19.0 whole and
+//    20.7 in 2, 1024 x 768 x 256 6.5 whole and 12.4 in 2. 64-wide tiles for
+//    launches with few 128-wide ones, once used, are slower since the operands
+//    are loaded directly (12544 x 256 x 2304: 28.2 against 23.4 us; 8192 x 512
+//    x 2048: 25.4 against 22.3).
+//  * SPLIT_OCCUPANCY (bottleneck stages): occupancy_splits. The order in which
+//    a product is summed is part of a bottleneck stage's results: its skips
+//    pass every ReLU mask of the outputs undamped to dX and v, and a different
+//    slice count in the 1x1 and 3x3 products moved v of two blocks by up to
+//    3.9e-2 (2-norm) at unchanged error against float64, more than the 3e-2
+//    that two versions of a stage may differ by. It costs: eight blocks at 14 x
+//    14, 64 images, 83.9 against 82.6 ms for 64 mini-batches; two blocks at 7 x
+//    7, 50 images, 48.3 against 48.9 for 96; the smallest stages up to 10 %.
 struct Shape {
   int ksl, splits;
 };
 
 constexpr double kStep = 0.4, kShared = 1.15, kReduce = 2.0, kPartial = 0.5;
 
-Shape shape_of(int M, int N, int K, int batch, size_t workspace_bytes, bool conv_gather) {
+// Slices that fill two blocks a CU, each at least 12 K steps long: none for
+// grids that 128 x 64 tiles would fill to three quarters, and beside another
+// pass none for grids of half the CUs' blocks unless K has 64 steps.
+int occupancy_splits(int M, int N, int K, int batch, size_t workspace_bytes, bool shared) {
+  const long rows = static_cast<long>((M + BM - 1) / BM) * batch;
+  const long t128 = rows * ((N + 127) / 128), t64 = rows * ((N + 63) / 64);
+  if (t128 >= 2 * kCUs || K < 2 * 12 * BK) return 1;
+  if (shared ? t128 >= kCUs / 2 && K < 64 * BK : 4 * t64 >= 6 * kCUs) return 1;
+  int splits = std::min({static_cast<int>(2 * kCUs / t128), K / (12 * BK), MAX_SPLITS});
+  const size_t plane = static_cast<size_t>(batch) * M * N * 4;
+  while (splits > 1 && splits * plane > workspace_bytes) --splits;
+  return splits;
+}
+
+Shape shape_of(int M, int N, int K, int batch, size_t workspace_bytes, bool conv_gather, SplitRule rule) {
   const long tiles = static_cast<long>((M + BM - 1) / BM) * ((N + BN - 1) / BN) * batch;
   Shape sh{1, 1};
-  if (conv_gather && tiles <= kCUs && 8 * tiles >= 7 * kCUs) {
+  const long half_tiles = static_cast<long>((M + BM - 1) / BM) * ((N + 63) / 64) * batch;
+  if (conv_gather && tiles <= kCUs && 8 * tiles >= 7 * kCUs && (rule == SPLIT_TIMED || 4 * half_tiles >= 6 * kCUs)) {
     sh.ksl = 2;
+    return sh;
+  }
+  if (rule != SPLIT_TIMED) {
+    sh.splits = occupancy_splits(M, N, K, batch, workspace_bytes, rule == SPLIT_OCCUPANCY_SHARED);
     return sh;
   }
   const int nk = (K + BK - 1) / BK;
@@ -1119,7 +1144,7 @@ bool plan(const GemmDesc& d, KArgs& a, hipError_t& err) {
   a.batch = d.batch;
   a.zdiv = zdiv;
   const bool gather = (d.A.mode == OP_K_CONV_FWD || d.A.mode == OP_K_CONV_DGRAD) && d.B.mode == OP_K_PLAIN;
-  const Shape sh = shape_of(d.M, d.N, d.K, d.batch, d.workspace ? d.workspace_bytes : 0, gather);
+  const Shape sh = shape_of(d.M, d.N, d.K, d.batch, d.workspace ? d.workspace_bytes : 0, gather, d.split_rule);
   a.ksl = sh.ksl;
   a.tiles_n = (d.N + BN - 1) / BN;
   a.tiles_total = a.tiles_n * ((d.M + BM - 1) / BM);
@@ -1217,9 +1242,9 @@ const char* gemm_bf16_reduce_name(const GemmDesc& d) {
   return a.vec_epi ? "splitk_reduce4_kernel<true>" : "splitk_reduce4_kernel<false>";
 }
 
-int gemm_bf16_split_rule(int M, int N, int K, int batch, size_t workspace_bytes) {
+int gemm_bf16_split_rule(int M, int N, int K, int batch, size_t workspace_bytes, SplitRule rule) {
   if (M <= 0 || N <= 0 || K <= 0 || batch <= 0) return 1;
-  return shape_of(M, N, K, batch, workspace_bytes, false).splits;
+  return shape_of(M, N, K, batch, workspace_bytes, false, rule).splits;
 }
 
 int gemm_bf16_splits(const GemmDesc& d) {

@@ -51,11 +51,16 @@ struct Epilogue {
   int accumulate = 0;              // out_f32 += value
 };
 
+// How the bf16 GEMM chooses the K slices of a launch: by modelled time, or to
+// fill the CUs (alone, or beside another pass's launches).
+enum SplitRule : int { SPLIT_TIMED = 0, SPLIT_OCCUPANCY = 1, SPLIT_OCCUPANCY_SHARED = 2 };
+
 struct GemmDesc {
   int M = 0, N = 0, K = 0;
   int batch = 1, zdiv = 1;
   float* workspace = nullptr;      // split-K partials (bf16 GEMM); NULL disables splitting
   size_t workspace_bytes = 0;
+  SplitRule split_rule = SPLIT_TIMED;
   int splits = 0;                  // K slices fixed by the caller (bf16 GEMM; they fit the workspace), 0: by rule
   Operand A, B;
   Epilogue epi;
@@ -68,7 +73,7 @@ enum { GEMM_MAIN = 1, GEMM_REDUCE = 2, GEMM_ALL = 3 };
 hipError_t gemm_bf16(const GemmDesc& d, hipStream_t s, int phases = GEMM_ALL);
 int gemm_bf16_splits(const GemmDesc& d);   // K splits the launch will use (1 = none)
 // The same count from the shape alone, for a workspace of workspace_bytes.
-int gemm_bf16_split_rule(int M, int N, int K, int batch, size_t workspace_bytes);
+int gemm_bf16_split_rule(int M, int N, int K, int batch, size_t workspace_bytes, SplitRule rule = SPLIT_TIMED);
 hipError_t gemm_f32(const GemmDesc& d, hipStream_t s);
 // Names of the kernels a launch runs, as a profiler lists the instantiations
 // (e.g. "gemm_bf16_kernel<0, 3, false, 1>"); the returned buffer is

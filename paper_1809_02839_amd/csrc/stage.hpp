@@ -152,6 +152,10 @@ class Stage {
   // store into g); when it splits K, its partials stay in the deferred buffer
   // and the update sums them instead of a separate reduction pass.
   void gemm(const GemmDesc& d, bool defer = false);
+  SplitRule split_rule() const {
+    if (d_.kind != SPECTRAIN_KIND_BOTTLENECK) return SPLIT_TIMED;
+    return concurrent_ ? SPLIT_OCCUPANCY_SHARED : SPLIT_OCCUPANCY;
+  }
   // A weight-gradient GEMM on the side stream: it waits for everything issued
   // on the stage stream so far (its inputs) and runs beside the data-gradient
   // chain that follows; join_side() makes the stage stream wait for all of
@@ -266,6 +270,7 @@ class Stage {
   std::vector<size_t> ws_off_;
   DeviceBlock ws_block_f_;               // workspace copy of a forward that runs beside a backward
   const DeviceBlock* wsb_ = &ws_block_;  // workspace of the pass being issued
+  bool concurrent_ = false;              // issuing the passes of forward_backward
   // workspace ids after the kind's own buffers: column-sum partials of the
   // stage stream and of the side stream, split-K partials of each stream
   int ws_colsum_ = -1, ws_colsum2_ = -1, ws_split_ = -1, ws_split2_ = -1;

@@ -53,13 +53,41 @@ int main() {
 """
 
 
-@pytest.mark.skipif(not os.path.exists(LIB), reason="the library has not been built here")
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
-def test_split_count_with_an_exactly_fitting_workspace(tmp_path):
+def _run(program, tmp_path):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run([HIPCC, "-x", "hip", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
                     "-packed-fp32-ops", "-std=c++17", "-O1", "-I", os.path.join(PKG, "csrc"), str(src), "-o", str(exe),
                     "-L", PKG, "-lspectrain", f"-Wl,-rpath,{PKG}"], check=True, capture_output=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+needs_build = pytest.mark.skipif(not (os.path.exists(LIB) and os.path.exists(HIPCC)),
+                                 reason="needs the built library and hipcc")
+
+
+@needs_build
+def test_split_count_with_an_exactly_fitting_workspace(tmp_path):
+    _run(PROGRAM, tmp_path)
+
+
+# (M, N, K): slices alone, and beside another pass. Two blocks a CU, at least 12
+# K steps a slice, at most 16; whole where 128 x 64 tiles fill three quarters of
+# the slots (alone), or from 128 tiles on below 64 K steps (beside).
+OCCUPANCY = {
+    (960, 480, 1920): (2, 2), (960, 480, 4320): (5, 5), (480, 1920, 960): (1, 1), (2450, 512, 2048): (2, 2),
+    (256, 1024, 12544): (16, 16), (256, 2304, 12544): (14, 14), (512, 4608, 2450): (3, 1), (24, 216, 2500): (3, 3),
+    (6272, 512, 4608): (1, 2), (19200, 64, 1600): (2, 1), (12544, 1024, 256): (1, 1),
+}
+
+
+@needs_build
+def test_occupancy_slices(tmp_path):
+    calls = "".join(f'std::printf("%d %d\\n", gemm_bf16_split_rule({m}, {n}, {k}, 1, 64u << 20, SPLIT_OCCUPANCY), '
+                    f'gemm_bf16_split_rule({m}, {n}, {k}, 1, 64u << 20, SPLIT_OCCUPANCY_SHARED));\n'
+                    for m, n, k in OCCUPANCY)
+    out = _run('#include <cstdio>\n#include "kernels.hpp"\nusing namespace spx;\nint main() {\n' + calls + "}\n",
+               tmp_path)
+    assert [tuple(map(int, l.split())) for l in out.splitlines()] == list(OCCUPANCY.values())

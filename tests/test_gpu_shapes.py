@@ -135,3 +135,19 @@ def test_filter_gradient_planes(batch, dims):
     del dirty
     torch.cuda.empty_cache()
     _run("conv3x3", "bf16", "none", batch, 1, dims, 1e-4)
+
+
+def test_bottleneck_products_keep_their_slices():
+    """A bottleneck's forward products are summed in 2 (1 x 1, K = 1920) and 5
+    (3 x 3, K = 4320) slices, as filling the CUs gives, not the 3 of the time
+    model: another order moves v of two blocks by 3.5e-2 here."""
+    from paper_1809_02839_amd import native
+    spec = synth.StageSpec("bottleneck", "bf16", "none", 0, 1, 15, 1, (1920, 480, 8, 8), 1e-6, 0.9)
+    st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
+    x = torch.from_numpy(synth.stage_input(spec, 0)).cuda().bfloat16()
+    st.profile(True)
+    st.forward(0, x, torch.empty_like(x))
+    torch.cuda.synchronize()
+    planes = sum(s["extra_bytes_total"] for n, s in st.profile_read().items() if n.startswith("gemm_bf16"))
+    st.destroy()
+    assert planes == 4 * 960 * 480 * (2 + 5)
