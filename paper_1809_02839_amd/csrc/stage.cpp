@@ -55,10 +55,36 @@ PinnedInts::~PinnedInts() {
   if (host_) (void)hipHostFree(host_);
 }
 
+long HostCopy::Ring::have(long want) {
+  for (long i = 0; i < want; ++i) {
+    if (slot[i]) continue;
+    if (hipHostMalloc(reinterpret_cast<void**>(&slot[i]), SLOT_FLOATS * sizeof(float), hipHostMallocPortable) !=
+        hipSuccess) {
+      (void)hipGetLastError();   // not an error of a later launch
+      slot[i] = nullptr;
+      return i;
+    }
+  }
+  return want;
+}
+
+HostCopy::Ring::~Ring() {
+  for (float* p : slot)
+    if (p) (void)hipHostFree(p);
+}
+
+std::shared_ptr<HostCopy::Ring> HostCopy::shared_ring() {
+  static std::mutex mu;
+  static std::weak_ptr<Ring> shared;
+  std::lock_guard<std::mutex> lock(mu);
+  std::shared_ptr<Ring> r = shared.lock();
+  if (!r) shared = r = std::make_shared<Ring>();
+  return r;
+}
+
 HostCopy::~HostCopy() {
   for (hipEvent_t e : done_)
     if (e) (void)hipEventDestroy(e);
-  if (ring_) (void)hipHostFree(ring_);
 }
 
 void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
@@ -67,27 +93,39 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
     const float* arena;
     float* packed;
     long off, n;
-    size_t slot;
+    long slot;
   };
   const long total = tensors.empty() ? 0 : tensors.back().off + tensors.back().n;
-  std::vector<Job> jobs;
-  for (const auto& a : arrays)
-    for (long o = 0; o < total; o += SLOT_FLOATS)
-      jobs.push_back({a.first, a.second, o, std::min(SLOT_FLOATS, total - o), jobs.size() % SLOTS});
-  if (!ring_) {
-    hip_check(hipHostMalloc(reinterpret_cast<void**>(&ring_), SLOTS * SLOT_FLOATS * sizeof(float), hipHostMallocDefault),
-              "hipHostMalloc");
+  if (!ring_) ring_ = shared_ring();
+  std::lock_guard<std::mutex> turn(ring_->mu);
+  const long chunks = (total + SLOT_FLOATS - 1) / SLOT_FLOATS * static_cast<long>(arrays.size());
+  const long slots = ring_->have(std::min(SLOTS, chunks));
+  if (slots == 0) {   // nothing to copy, or no pinned memory to be had
+    std::vector<float> h(arrays.empty() ? 0 : total);
+    for (const auto& a : arrays) {
+      hip_check(hipMemcpy(h.data(), a.first, total * sizeof(float), hipMemcpyDeviceToHost), "copy to host");
+      long at = 0;
+      for (const TensorInfo& t : tensors) {
+        std::memcpy(a.second + at, h.data() + t.off, t.n * sizeof(float));
+        at += t.n;
+      }
+    }
+    return;
   }
   for (hipEvent_t& e : done_)
     if (!e) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
+  std::vector<Job> jobs;
+  for (const auto& a : arrays)
+    for (long o = 0; o < total; o += SLOT_FLOATS)
+      jobs.push_back({a.first, a.second, o, std::min(SLOT_FLOATS, total - o), static_cast<long>(jobs.size()) % slots});
 
   std::mutex mu;
   std::condition_variable cv;
   std::deque<const Job*> ready;      // copied to their slot, to be moved to the destination
   bool busy[SLOTS] = {};
-  bool end = false;
+  bool end = false, whole = false;
   auto move = [&](const Job& j) {   // the tensors' parts of the range, without the arena's padding
-    const float* src = ring_ + j.slot * SLOT_FLOATS;
+    const float* src = ring_->slot[j.slot];
     long at = 0;
     for (const TensorInfo& t : tensors) {
       const long b = std::max(t.off, j.off), e = std::min(t.off + t.n, j.off + j.n);
@@ -111,9 +149,10 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
   };
   std::vector<std::thread> threads;
   struct Joiner {                    // also where a copy below fails
+    hipStream_t s;
     std::mutex& mu;
     std::condition_variable& cv;
-    bool& end;
+    bool &end, &whole;
     std::vector<std::thread>& t;
     ~Joiner() {
       {
@@ -122,8 +161,9 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
       }
       cv.notify_all();
       for (std::thread& x : t) x.join();
+      if (!whole) (void)hipStreamSynchronize(s);   // no copy into the ring is left for its next user to meet
     }
-  } joiner{mu, cv, end, threads};
+  } joiner{s, mu, cv, end, whole, threads};
   // threads cost about 0.1 ms to start and join: from two full slots on
   const size_t want = total * static_cast<long>(arrays.size()) < 2 * SLOT_FLOATS ? 0 : std::min<size_t>(4, jobs.size());
   threads.reserve(want);
@@ -135,7 +175,7 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
   size_t issued = 0;
   for (size_t i = 0; i < jobs.size(); ++i) {
     // keep the ring full ahead of the job awaited next
-    while (issued < jobs.size() && issued < i + SLOTS) {
+    while (issued < jobs.size() && issued < i + static_cast<size_t>(slots)) {
       const Job& j = jobs[issued];
       {
         std::unique_lock<std::mutex> lock(mu);
@@ -145,7 +185,7 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
         }
         busy[j.slot] = true;
       }
-      hip_check(hipMemcpyAsync(ring_ + j.slot * SLOT_FLOATS, j.arena + j.off, j.n * sizeof(float),
+      hip_check(hipMemcpyAsync(ring_->slot[j.slot], j.arena + j.off, j.n * sizeof(float),
                                hipMemcpyDeviceToHost, s),
                 "copy to host");
       hip_check(hipEventRecord(done_[j.slot], s), "hipEventRecord");
@@ -164,6 +204,7 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
     }
     cv.notify_all();
   }
+  whole = true;
 }
 
 namespace {

@@ -6,6 +6,8 @@
 #include <cstdio>
 #include <initializer_list>
 #include <map>
+#include <memory>
+#include <mutex>
 #include <stdexcept>
 #include <string>
 #include <utility>
@@ -81,19 +83,29 @@ struct TensorInfo {
 // through a ring of pinned buffers, the host side spread over a few threads.
 // Most of such a copy is the host's: one thread touching the destination's
 // pages for the first time moved 4.5 GB/s through a pageable copy and a
-// second pass over the data (71 MB in 15.8 ms; now 2.2 ms).
+// second pass over the data (64 MiB in 15.6 ms; now 2.9; 4 MiB in 0.42 and
+// 0.22). The ring, at most 12 MiB, is one for the process, made slot by slot
+// as copies need it, held by every stage that has copied and freed with the
+// last of them; one copy uses it at a time. Where its first slot cannot be
+// had, the copy goes the pageable way.
 class HostCopy {
  public:
   // Copies the tensors of each (device arena, packed host array) pair on
-  // stream s and returns when all are in place. The pinned ring is made on the
-  // first use and kept with the owner.
+  // stream s and returns when all are in place.
   void run(const std::vector<std::pair<const float*, float*>>& arrays, const std::vector<TensorInfo>& tensors,
            hipStream_t s);
   ~HostCopy();
 
  private:
   static constexpr long SLOTS = 6, SLOT_FLOATS = 1L << 19;   // 6 x 2 MiB
-  float* ring_ = nullptr;
+  struct Ring {
+    std::mutex mu;
+    float* slot[SLOTS] = {};
+    long have(long want);   // slots present after trying to make `want` of them
+    ~Ring();
+  };
+  static std::shared_ptr<Ring> shared_ring();
+  std::shared_ptr<Ring> ring_;
   hipEvent_t done_[SLOTS] = {};
 };
 
