@@ -55,6 +55,18 @@ PinnedInts::~PinnedInts() {
   if (host_) (void)hipHostFree(host_);
 }
 
+DeviceGuard::DeviceGuard(int device) {
+  int current = -1;
+  hip_check(hipGetDevice(&current), "hipGetDevice");
+  if (current == device) return;
+  hip_check(hipSetDevice(device), "hipSetDevice");
+  before_ = current;
+}
+
+DeviceGuard::~DeviceGuard() {
+  if (before_ >= 0) (void)hipSetDevice(before_);
+}
+
 long HostCopy::Ring::have(long want) {
   for (long i = 0; i < want; ++i) {
     if (slot[i]) continue;
@@ -80,6 +92,10 @@ std::shared_ptr<HostCopy::Ring> HostCopy::shared_ring() {
   std::shared_ptr<Ring> r = shared.lock();
   if (!r) shared = r = std::make_shared<Ring>();
   return r;
+}
+
+void HostCopy::init() {
+  for (hipEvent_t& e : done_) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
 }
 
 HostCopy::~HostCopy() {
@@ -112,8 +128,6 @@ void HostCopy::run(const std::vector<std::pair<const float*, float*>>& arrays,
     }
     return;
   }
-  for (hipEvent_t& e : done_)
-    if (!e) hip_check(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
   std::vector<Job> jobs;
   for (const auto& a : arrays)
     for (long o = 0; o < total; o += SLOT_FLOATS)
@@ -708,6 +722,7 @@ Stage::Stage(const spectrain_stage_desc& d, const float* W0, size_t n_params, hi
   hip_check(hipStreamCreateWithFlags(&s3_, hipStreamNonBlocking), "hipStreamCreate");
   hip_check(hipEventCreateWithFlags(&ffork_ev_, hipEventDisableTiming), "hipEventCreate");
   hip_check(hipEventCreateWithFlags(&fjoin_ev_, hipEventDisableTiming), "hipEventCreate");
+  host_copy_.init();
   // arenas: W, v, g (float32), two predicted slots (operand dtype), all padded
   size_t oW = arena_.add(n_arena_ * 4), ov = arena_.add(n_arena_ * 4), og = arena_.add(n_arena_ * 4);
   size_t of = arena_.add(n_arena_ * esz_), ob = arena_.add(n_arena_ * esz_);
@@ -776,6 +791,7 @@ void Stage::set_state(const float* W, const float* v) {
 }
 
 void Stage::get_state(float* W, float* v) {
+  const DeviceGuard on(device_);   // the calling thread may have another current
   sync();
   std::vector<std::pair<const float*, float*>> arrays;
   if (W) arrays.emplace_back(W_, W);

@@ -90,8 +90,11 @@ struct TensorInfo {
 // had, the copy goes the pageable way.
 class HostCopy {
  public:
+  // Makes the events, on the current device (the stream's).
+  void init();
   // Copies the tensors of each (device arena, packed host array) pair on
-  // stream s and returns when all are in place.
+  // stream s and returns when all are in place. The current device is the
+  // stream's.
   void run(const std::vector<std::pair<const float*, float*>>& arrays, const std::vector<TensorInfo>& tensors,
            hipStream_t s);
   ~HostCopy();
@@ -107,6 +110,16 @@ class HostCopy {
   static std::shared_ptr<Ring> shared_ring();
   std::shared_ptr<Ring> ring_;
   hipEvent_t done_[SLOTS] = {};
+};
+
+// Makes a device current for a scope.
+class DeviceGuard {
+ public:
+  explicit DeviceGuard(int device);
+  ~DeviceGuard();
+
+ private:
+  int before_ = -1;
 };
 
 class Stage {
