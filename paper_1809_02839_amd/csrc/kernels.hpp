@@ -115,9 +115,9 @@ hipError_t fused_update_partials(float* W, float* v, const float* g, const Updat
                                  int s_b, int* flag, hipStream_t s);
 
 // Fused residual-LSTM recurrence steps (supported for H a multiple of 8 and
-// batches up to the size where a GEMM and a cell launch are as fast): forward
-// z_t = zx_t + h_{t-1} W_h^T and the cell in one launch; backward dh_t = dh_out_t + dz_{t+1} W_h (W_h^T given) and the
-// cell backward in one launch. Null h_prev / c_prev mark the first step, null
+// sizes up to where a GEMM and a cell launch are as fast): forward z_t = zx_t +
+// h_{t-1} W_h^T and the cell in one launch; backward dh_t = dh_out_t + dz_{t+1}
+// W_h (W_h^T given) and the cell backward in one launch. Null h_prev / c_prev mark the first step, null
 // dz_next the last one (dc then starts at zero and need not be set).
 bool lstm_step_supported(int B, int H);
 hipError_t lstm_step_fwd(const float* zx_t, const bf16_t* h_prev, const bf16_t* Wh, const float* c_prev, int B, int H,

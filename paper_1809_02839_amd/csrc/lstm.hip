@@ -264,14 +264,22 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16_t* X, in
 }  // namespace
 
 // Where one fused launch per step beats a GEMM and a cell launch. A fused step
-// re-reads its operands per 32 (16) batch rows, so its time grows with B H
-// once the grid is more than one block per CU; the GEMM path is a flat 30 us
-// (forward) until its own grid fills the chip. Both measured, us per step of a
-// one-layer stage, T = 16: H = 1024: B = 128 672 against 787, B = 192 914
-// against 880; H = 512: B = 100 282 against 632, B = 384 599 against 717;
-// H = 256: B = 512 340 against 614. The line is 160 rows at H = 1024.
+// reads H (4 H backward) contraction steps in every block and runs its blocks
+// of 32 (16) rows and 8 (16) units in rounds of the CUs, so its time grows with
+// the rounded rows times H^2, and for small H with B H; the GEMM path is about
+// 25 us a time step until its own grid fills the chip. Both sides measured, us
+// of a one-layer step with T = 16, fused against GEMM:
+//   H = 256:  B = 1024 533 / 638, 1536 780 / 721
+//   H = 512:  B = 320 549 / 644, 512 732 / 743, 640 903 / 809
+//   H = 1024: B = 64 390 / 552, 128 644 / 758, 160 856 / 816
+//   H = 1536: B = 32 567 / 644, 48 843 / 709, 96 1196 / 849
+//   H = 2048: B = 32 800 / 810, 64 1239 / 944
+//   H = 2560: B = 8 943 / 993, 32 1522 / 1164;  H = 3072: B = 64 2590 / 1693
+//   H = 64:   B = 4096 463 / 561, 16384 1624 / 1210;  H = 128: B = 4096 869 / 748
 bool lstm_step_supported(int B, int H) {
-  return B >= 1 && H >= 8 && H % 8 == 0 && static_cast<long>(B) * H <= 160L * 1024;
+  if (B < 1 || H < 8 || H % 8 || static_cast<long>(B) * H > 256L * 1024) return false;
+  const long rows = B <= 16 ? 16 : (B + 31) / 32 * 32;
+  return rows * H * H <= 140L << 20;
 }
 
 hipError_t lstm_step_fwd(const float* zx_t, const bf16_t* h_prev, const bf16_t* Wh, const float* c_prev, int B,

@@ -1,7 +1,10 @@
-"""Host check on the launch plan of the bf16 GEMM, asked from the built
-library: a workspace that holds exactly the K slices the rule chose gives the
-same count again. The update sums that many partial planes, so a launch that
-took fewer would leave it planes that nobody wrote."""
+"""Host checks on the dispatch rules, asked from the built library.
+
+bf16 GEMM: a workspace that holds exactly the K slices the rule chose gives the
+same count again (the update sums that many partial planes, so a launch that
+took fewer would leave it planes that nobody wrote), and bottleneck stages take
+the slices that fill the CUs. LSTM: the rule takes the faster path where both
+were measured."""
 import os
 import subprocess
 
@@ -91,3 +94,30 @@ def test_occupancy_slices(tmp_path):
     out = _run('#include <cstdio>\n#include "kernels.hpp"\nusing namespace spx;\nint main() {\n' + calls + "}\n",
                tmp_path)
     assert [tuple(map(int, l.split())) for l in out.splitlines()] == list(OCCUPANCY.values())
+
+
+# us of a one-layer step (T = 16, forward, backward and update), one fused
+# launch per time step against a GEMM and a cell launch, by (H, B).
+LSTM_TIMES = {
+    (8, 4096): (226, 458), (8, 16384): (559, 703), (64, 1024): (205, 470), (64, 4096): (463, 561),
+    (64, 16384): (1624, 1210), (128, 4096): (869, 748), (256, 256): (230, 511), (256, 1024): (533, 638),
+    (256, 1536): (780, 721), (512, 64): (254, 524), (512, 320): (549, 644), (512, 512): (732, 743),
+    (512, 640): (903, 809), (776, 224): (699, 773), (1024, 8): (300, 484), (1024, 64): (390, 552),
+    (1024, 128): (644, 758), (1024, 160): (856, 816), (1024, 256): (1128, 939), (1032, 100): (668, 777),
+    (1280, 64): (718, 672), (1280, 80): (752, 713), (1536, 32): (567, 644), (1536, 48): (843, 709),
+    (1536, 96): (1196, 849), (2048, 16): (705, 764), (2048, 32): (800, 810), (2048, 64): (1239, 944),
+    (2560, 8): (943, 993), (2560, 32): (1522, 1164), (3072, 64): (2590, 1693), (4096, 32): (2771, 2175),
+}
+
+
+@needs_build
+def test_lstm_rule_takes_the_faster_path(tmp_path):
+    calls = "".join(f'std::printf("%d\\n", int(lstm_step_supported({b}, {h})));\n' for h, b in LSTM_TIMES)
+    calls += 'std::printf("%d %d %d %d\\n", int(lstm_step_supported(0, 64)), int(lstm_step_supported(4, 0)), ' \
+             'int(lstm_step_supported(4, 68)), int(lstm_step_supported(1 << 30, 8)));\n'
+    *got, refused = _run('#include <cstdio>\n#include "kernels.hpp"\nusing namespace spx;\nint main() {\n' + calls +
+                         "}\n", tmp_path).splitlines()
+    assert refused == "0 0 0 0"
+    slower = {hb: (t[1 - int(g)], t[int(g)]) for (hb, t), g in zip(LSTM_TIMES.items(), got)
+              if (t[0] if int(g) else t[1]) > 1.07 * min(t)}
+    assert not slower, slower

@@ -33,8 +33,7 @@ def test_float32_products(head, batch, layers, dims):
 
 # dims (H, H, T[, vocab]): H no multiple of 32 (short last k fragment) nor of 16
 # (short last unit block of the backward); batches past one row block of either
-# direction with remainders; the largest batch of the fused steps and the first
-# past it (a GEMM and a cell launch per step).
+# direction with remainders; ten whole row blocks and one row past them.
 @pytest.mark.parametrize("head,batch,dims", [
     ("none", 1, (8, 8, 3, 8)), ("ce", 33, (72, 72, 4, 24)), ("none", 100, (40, 40, 3, 8)), ("none", 65, (1032, 1032, 3, 8)),
     ("none", 320, (512, 512, 3, 8)), ("none", 321, (512, 512, 3, 8)),
@@ -151,3 +150,26 @@ def test_bottleneck_products_keep_their_slices():
     planes = sum(s["extra_bytes_total"] for n, s in st.profile_read().items() if n.startswith("gemm_bf16"))
     st.destroy()
     assert planes == 4 * 960 * 480 * (2 + 5)
+
+
+# Either side of the rule's lines: the largest batch of the fused steps and the
+# first of a GEMM and a cell launch per step, by rows H^2 and by B H.
+@pytest.mark.parametrize("batch,H,fused", [
+    (512, 512, True), (513, 512, False), (128, 1024, True), (129, 1024, False), (8, 2560, True), (17, 2560, False),
+    (1024, 256, True), (1025, 256, False),
+])
+def test_lstm_rule(batch, H, fused):
+    from paper_1809_02839_amd import native
+    spec = synth.StageSpec("reslstm", "bf16", "none", 0, 1, batch, 1, (H, H, 2, 8), 1e-2, 0.9)
+    st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
+    x = torch.from_numpy(synth.stage_input(spec, 0)).cuda().bfloat16()
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    st.profile(True)
+    st.forward(0, x, y)
+    st.backward(0, torch.ones_like(x) / x.numel(), dx)
+    torch.cuda.synchronize()
+    names = set(st.profile_read())
+    st.destroy()
+    assert {"lstm_step", "lstm_step_bwd"} <= names if fused else {"lstm_cell", "lstm_cell_bwd"} <= names
+    if H == 512:
+        _run("reslstm", "bf16", "none", batch, 1, (H, H, 2, 8), 1e-2, steps=3)
