@@ -179,8 +179,8 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(F32Args a) {
   }
 }
 
-// Eight elements k, k + 1, .. k + 7 of one row (zero past kend or for a row
-// outside the operand) as two groups of four.
+// Four elements k .. k + 3 of one row (zero past kend or for a row outside the
+// operand).
 template <int MODE, bool VEC>
 __device__ __forceinline__ void short_load(const float* X, long ld, bool ok, int row, int k, int kend, float4& v) {
   v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -267,13 +267,20 @@ __global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(F32Args a) {
   }
 }
 
-// Kernel and K split of a product. The short kernel serves grids whose waves
-// run few rounds one after the other: up to 256K (32 x 32 tile, k) pairs, so
-// at most 256 rounds of loads over all blocks of a CU-wide grid. A product of
-// 32 x 256 x 784 takes one launch instead of two (the three-layer classifier:
-// 113 -> 88 us a mini-batch); past the limit the tile kernel's reuse of each
-// load 64 times wins (128 x 2048 x 3072: 105 us with the former 16-deep,
-// element-loading tile; a step of three such layers 851 -> 229 us).
+// Kernel and K split of a product. The short kernel serves grids of few waves
+// whose blocks run few rounds one after the other: at most four rounds of
+// SW SCH = 256 k (2 us each, which no idle CU shortens),
+// and up to 256K (32 x 32 tile, k) pairs, past which the tile kernel's reuse of
+// each load 64 times wins. us, short against tile kernel with its reduction:
+//   32 x 10:   K = 256 7.9 / 11.5, 512 8.9 / 11.4, 1024 12.5 / 12.4,
+//              2048 20.1 / 13.0, 8192 63 / 15.5, 65536 494 / 36, 262144 1970 / 110
+//   256 x 128: K = 256 8.4 / 11.4, 1024 14.5 / 13.6, 2048 23.2 / 14.3
+//   512 x 256: K = 256 8.4 / 11.7, 1024 14.9 / 14.6, 2048 25.8 / 19.1
+// At 1024 the one launch saved decides. A product of 32 x 256 x 784 takes one
+// launch instead of two (the three-layer classifier: 113 -> 88 us a
+// mini-batch); 128 x 2048 x 3072, long since past the limits, took 105 us with
+// the former 16-deep, element-loading tile (a step of three such layers 851 ->
+// 229 us).
 struct Pick {
   bool short_k;
   int splits, steps_per;
@@ -284,7 +291,7 @@ Pick pick(int M, int N, int K, bool ws, size_t ws_bytes) {
   const long t64 = static_cast<long>((M + TB - 1) / TB) * ((N + TB - 1) / TB);
   const int ksteps = (K + TK - 1) / TK;
   Pick p{false, 1, std::max(1, ksteps)};
-  if (t32 <= 1024 && static_cast<long>(K) * t32 <= 256L * 1024) {
+  if (K <= 4 * SW * SCH && t32 <= 1024 && K * t32 <= 256L * 1024) {
     p.short_k = true;
     return p;
   }

@@ -3,8 +3,8 @@
 bf16 GEMM: a workspace that holds exactly the K slices the rule chose gives the
 same count again (the update sums that many partial planes, so a launch that
 took fewer would leave it planes that nobody wrote), and bottleneck stages take
-the slices that fill the CUs. LSTM: the rule takes the faster path where both
-were measured."""
+the slices that fill the CUs. LSTM and float32 GEMM: the rules take the faster
+path where both were measured."""
 import os
 import subprocess
 
@@ -120,4 +120,38 @@ def test_lstm_rule_takes_the_faster_path(tmp_path):
     assert refused == "0 0 0 0"
     slower = {hb: (t[1 - int(g)], t[int(g)]) for (hb, t), g in zip(LSTM_TIMES.items(), got)
               if (t[0] if int(g) else t[1]) > 1.07 * min(t)}
+    assert not slower, slower
+
+
+# us of a float32 product X W^T on the short and on the tile kernel (with its
+# reduction), by (M, N, K).
+F32_TIMES = {
+    (32, 10, 128): (6.5, 9.9), (32, 10, 512): (8.9, 11.4), (32, 10, 2048): (20.1, 13.0), (32, 10, 16384): (124, 17.7),
+    (32, 10, 262144): (1970, 110), (64, 64, 256): (8.0, 11.4), (64, 64, 4096): (40.3, 14.3),
+    (128, 64, 512): (10.5, 11.8), (128, 128, 2048): (23.5, 13.9), (256, 128, 8192): (76.1, 20.1),
+    (256, 256, 512): (10.0, 12.6), (256, 256, 4096): (42.2, 19.0), (512, 256, 256): (8.4, 11.7),
+    (512, 256, 2048): (25.8, 19.1),
+}
+
+
+@needs_build
+def test_float32_rule_takes_the_faster_kernel(tmp_path):
+    calls = "".join(f"std::puts(name({m}, {n}, {k}));\n" for m, n, k in F32_TIMES)
+    got = _run("""#include <cstdio>
+#include "kernels.hpp"
+using namespace spx;
+const char* name(int m, int n, int k) {
+  GemmDesc d;
+  d.M = m;
+  d.N = n;
+  d.K = k;
+  d.A.ld = d.B.ld = k;
+  d.workspace = reinterpret_cast<float*>(256);   // an address only: nothing is launched
+  d.workspace_bytes = 8u << 20;
+  return gemm_f32_kernel_name(d);
+}
+int main() {
+""" + calls + "}\n", tmp_path).split("\n")
+    slower = {p: t for (p, t), g in zip(F32_TIMES.items(), got)
+              if t[0 if g.startswith("gemm_f32_short") else 1] > 1.05 * min(t)}
     assert not slower, slower
