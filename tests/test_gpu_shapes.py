@@ -21,8 +21,9 @@ def _run(kind, dtype, head, batch, layers, dims, lr, k=1, N=3, steps=5):
 
 # dims (in, out, hidden). One value in one layer; 32 x 32 tiles with remainders
 # and K below one wave's share; the same with leading dimensions and extents
-# that no 16-byte load fits; products past the short kernel's limit, whole
-# tiles and split K, then ragged 64 x 64 tiles without and with vector loads.
+# that no 16-byte load fits; the short kernel's largest K; products past it by
+# three (ragged 64 x 64 tiles, element loads), and a weight gradient past the
+# short kernel's tile limit with vector loads.
 @pytest.mark.parametrize("head,batch,layers,dims", [
     ("none", 1, 1, (1, 1, 1)), ("ce", 31, 2, (64, 10, 36)), ("ce", 33, 2, (131, 7, 65)),
     ("none", 128, 2, (1024, 256, 1024)), ("none", 67, 2, (1027, 259, 514)), ("ce", 130, 2, (516, 1000, 1036)),
@@ -173,3 +174,26 @@ def test_lstm_rule(batch, H, fused):
     assert {"lstm_step", "lstm_step_bwd"} <= names if fused else {"lstm_cell", "lstm_cell_bwd"} <= names
     if H == 512:
         _run("reslstm", "bf16", "none", batch, 1, (H, H, 2, 8), 1e-2, steps=3)
+
+
+# Products on the 64 x 64 tiles in every operand mode: whole tiles with 16-byte
+# loads, K in 8, 5 and 4 slices; and sizes that no tile, K step or 16-byte load
+# fits, K in 3 and 5 slices of which the last is short (element loads).
+@pytest.mark.parametrize("head,batch,dims,vec", [
+    ("ce", 128, (3072, 10, 2048), "true"), ("none", 131, (3075, 259, 2051), "false"),
+])
+def test_float32_tiles(head, batch, dims, vec):
+    from paper_1809_02839_amd import native
+    spec = synth.StageSpec("fc", "fp32", head, 0, 1, batch, 3, dims, 1e-2, 0.9)
+    st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
+    x = torch.from_numpy(synth.stage_input(spec, 0)).cuda().float()
+    y = torch.empty(batch, dims[1], device="cuda") if head == "none" else None
+    lab = torch.zeros(batch, dtype=torch.int32, device="cuda") if head == "ce" else None
+    st.profile(True)
+    st.forward(0, x, y, lab, torch.zeros(1, device="cuda") if head == "ce" else None)
+    st.backward(0, y, torch.empty_like(x))
+    torch.cuda.synchronize()
+    names = set(st.profile_read())
+    st.destroy()
+    assert {f"gemm_f32_kernel<{m}, {vec}>" for m in ("0, 0", "0, 3", "3, 3")} <= names, names
+    _run("fc", "fp32", head, batch, 3, dims, 1e-2, steps=3)
