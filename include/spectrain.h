@@ -285,8 +285,8 @@ int spectrain_stage_profile_read(spectrain_stage_t st, spectrain_kernel_stat* ou
  *               (l < L-1, or every block with a CE head); 3L: pooled [B, C], 3L+1: dlogits
  *   TRANSFORMER 13l+j: 0 qkv [T, 3d], 1 softmax row statistics (max, 1/sum) f32 [B*heads*S, 2]
  *               (sequence 128, head dimension 64) or probabilities f32 [B*heads, S, S],
- *               2 probabilities bf16 (the second form only; both recomputed by this call, in
- *               temporary device memory, at head dimensions 32 and 64), 3 ctx [T, d], 4 r1 = x + attention
+ *               2 probabilities bf16 (the second form only; at head dimensions 32 and 64 this call
+ *               forms both from qkv and the stored row statistics, as the passes do), 3 ctx [T, d], 4 r1 = x + attention
  *               output [T, d], 5 mean of r1 f32 [T], 6 1/std of r1 f32 [T], 7 h = LN1(r1) [T, d],
  *               8 ReLU(FFN1) [T, F], 9 r2 = h + FFN2 [T, d], 10 mean of r2 f32, 11 1/std of r2 f32,
  *               12 layer output [T, d] (l < L-1, or every layer with a CE head);

@@ -381,6 +381,47 @@ __global__ __launch_bounds__(NT, 2) void attention_long_dkv_kernel(const bf16_t*
   store_rows<DH>(out + 2 * d, at.ld, key, S, dv, 1.0f, lane);
 }
 
+// Probabilities of 32 query rows of one (batch, head) for a reader, formed from
+// the stored statistics by the operations of the passes above, so they are the
+// values those passes use: the float32 P (Pf) or bf16(P) (Pb). Unit u covers
+// rows 32 (u % units) .. of head u / units; the output starts at unit u0's.
+template <int DH>
+__global__ __launch_bounds__(64) void attention_long_probs_kernel(const bf16_t* qkv, const float* stats, int S,
+                                                                  int heads, int d, float scale, long u0, float* Pf,
+                                                                  bf16_t* Pb) {
+  const int lane = threadIdx.x, units = (S + 31) / 32;
+  const long u = u0 + blockIdx.x, z = u / units, z0 = u0 / units;
+  const int row0 = static_cast<int>(u - z * units) * 32, row = row0 + (lane & 31), rc = min(row, S - 1);
+  const long ld = 3L * d, b = z / heads;
+  const bf16_t* q = qkv + b * S * ld + (z - b * heads) * DH;
+  const bf16_t* k = q + d;
+  bf16x8_t fq[DH / 16];
+  load_frags<DH>(q + rc * ld, lane, fq);
+  const float m = stats[2 * (z * S + rc)], inv = stats[2 * (z * S + rc) + 1];
+  const long first = z0 * S + 32L * (u0 - z0 * units);   // row of the output's first
+  for (int c0 = 0; c0 < S; c0 += 32) {
+    bf16x8_t fk[DH / 16];
+    load_frags<DH>(k + min(c0 + (lane & 31), S - 1) * ld, lane, fk);
+    f32x16_t p;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < DH / 16; ++e) p = mfma(fk[e], fq[e], p);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = __fmul_rn(exp_neg(__fsub_rn(__fmul_rn(p[r], scale), m)), inv);
+    if (row >= S) continue;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int c = c0 + col_of(4 * g, lane);   // S is a multiple of 8: the four columns are inside or outside
+      if (c >= S) continue;
+      const long at = (z * S + row - first) * S + c;
+      if (Pf) *reinterpret_cast<float4*>(Pf + at) = make_float4(p[4 * g], p[4 * g + 1], p[4 * g + 2], p[4 * g + 3]);
+      else *reinterpret_cast<uint2*>(Pb + at) = make_uint2(pack_bf16x2(p[4 * g], p[4 * g + 1]),
+                                                           pack_bf16x2(p[4 * g + 2], p[4 * g + 3]));
+    }
+  }
+}
+
 }  // namespace
 
 // Head dimensions the tiles are compiled for; the grid's second dimension
@@ -395,6 +436,18 @@ hipError_t attention_long_fwd(const bf16_t* qkv, int batch, int S, int heads, in
   const dim3 grid((S + TS - 1) / TS, batch * heads);
   auto* kernel = d / heads == 64 ? attention_long_fwd_kernel<64> : attention_long_fwd_kernel<32>;
   hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, s, qkv, S, heads, d, scale, stats, ctx);
+  return hipGetLastError();
+}
+
+hipError_t attention_long_probs(const bf16_t* qkv, const float* stats, int batch, int S, int heads, int d, float scale,
+                                long u0, long u1, float* Pf, bf16_t* Pb, hipStream_t s) {
+  const long units = static_cast<long>(batch) * heads * ((S + 31) / 32);
+  if (!attention_long_supported(batch, heads, d / heads) || S < 1 || S % 8 || u0 < 0 || u1 <= u0 || u1 > units ||
+      u1 - u0 > 0x7fffffff)
+    return hipErrorInvalidValue;
+  auto* kernel = d / heads == 64 ? attention_long_probs_kernel<64> : attention_long_probs_kernel<32>;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(u1 - u0)), dim3(64), 0, s, qkv, stats, S, heads, d, scale, u0,
+                     Pf, Pb);
   return hipGetLastError();
 }
 

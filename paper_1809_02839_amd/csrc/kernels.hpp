@@ -143,6 +143,11 @@ hipError_t attention_bwd(const bf16_t* qkv, const bf16_t* dctx, const float* sta
 bool attention_long_supported(int batch, int heads, int head_dim);
 hipError_t attention_long_fwd(const bf16_t* qkv, int batch, int S, int heads, int d, float scale, float* stats,
                               bf16_t* ctx, hipStream_t s);
+// Probabilities from qkv and the forward's statistics, float32 (Pf) or bf16
+// (Pb, with Pf null): rows of units [u0, u1), a unit being up to 32 rows of a
+// (batch, head), the output starting at unit u0's first row.
+hipError_t attention_long_probs(const bf16_t* qkv, const float* stats, int batch, int S, int heads, int d, float scale,
+                                long u0, long u1, float* Pf, bf16_t* Pb, hipStream_t s);
 hipError_t attention_long_bwd(const bf16_t* qkv, const bf16_t* dctx, const float* stats, int batch, int S, int heads,
                               int d, float scale, float* dots, bf16_t* dqkv, hipStream_t s);
 

@@ -832,13 +832,26 @@ size_t Stage::read_stash(int64_t mb, int index, void* host, size_t capacity) {
   sync();
   if (d_.kind == SPECTRAIN_KIND_TRANSFORMER && attention() == Attention::kTiles && index < 13 * d_.num_layers &&
       (index % 13 == 1 || index % 13 == 2)) {
-    const size_t count = stash_bytes_[index - index % 13 + 2] / 2;
-    DeviceBlock tmp;
-    const size_t os = tmp.add(count * 4), op = tmp.add(count * 4), ob = tmp.add(count * 2);
-    tmp.allocate();
-    attention_probs(stash<bf16_t>(slot, index - index % 13), tmp.at<float>(os), tmp.at<float>(op), tmp.at<bf16_t>(ob));
-    sync();
-    hip_check(hipMemcpy(host, tmp.at<char>(index % 13 == 1 ? op : ob), n, hipMemcpyDeviceToHost), "copy stash");
+    // from the stored statistics, in as many parts as the split-K workspace
+    // (no pass is using it) makes of them
+    const int B = d_.batch, d = d_.dims[0], heads = d_.dims[1], S = d_.dims[3], per_head = (S + 31) / 32;
+    const bool f32 = index % 13 == 1;
+    const size_t row = static_cast<size_t>(S) * (f32 ? 4 : 2);
+    const long units = static_cast<long>(B) * heads * per_head, step = static_cast<long>(gemm_ws_bytes_ / (32 * row));
+    if (step < 1) fail("sequence too long for the workspace");
+    float* const part = ws<float>(ws_split_);
+    auto first_row = [&](long u) { return u / per_head * S + 32 * (u % per_head); };
+    for (long u = 0; u < units; u += step) {
+      const long end = std::min(units, u + step);
+      hip_check(attention_long_probs(stash<bf16_t>(slot, index - index % 13), stash<float>(slot, index - index % 13 + 1),
+                                     B, S, heads, d, 1.0f / std::sqrt(static_cast<float>(d / heads)), u, end,
+                                     f32 ? part : nullptr, reinterpret_cast<bf16_t*>(part), s_),
+                "attention_long_probs");
+      sync();
+      hip_check(hipMemcpy(static_cast<char*>(host) + first_row(u) * row, part, (first_row(end) - first_row(u)) * row,
+                          hipMemcpyDeviceToHost),
+                "copy stash");
+    }
     return n;
   }
   hip_check(hipMemcpy(host, slot_blocks_[slot].at<char>(stash_off_[index]), n, hipMemcpyDeviceToHost), "copy stash");

@@ -177,8 +177,8 @@ def test_lstm_rule(batch, H, fused):
 
 
 # Products on the 64 x 64 tiles in every operand mode: whole tiles with 16-byte
-# loads, K in 8, 5 and 4 slices; and sizes that no tile, K step or 16-byte load
-# fits, K in 3 and 5 slices of which the last is short (element loads).
+# loads, K in 5 to 16 slices; and sizes that no tile, K step or 16-byte load
+# fits, K in 3 to 13 slices of which the last is short (element loads).
 @pytest.mark.parametrize("head,batch,dims,vec", [
     ("ce", 128, (3072, 10, 2048), "true"), ("none", 131, (3075, 259, 2051), "false"),
 ])
@@ -197,3 +197,36 @@ def test_float32_tiles(head, batch, dims, vec):
     st.destroy()
     assert {f"gemm_f32_kernel<{m}, {vec}>" for m in ("0, 0", "0, 3", "3, 3")} <= names, names
     _run("fc", "fp32", head, batch, 3, dims, 1e-2, steps=3)
+
+
+def _bf(a):
+    import numpy as np
+    return (a.view(np.uint16).astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("dims", [(64, 2, 72, 136), (128, 2, 136, 40)])
+def test_stash_probabilities_are_the_passes_own(dims):
+    """The context is bf16(P) V of the probabilities that read_stash returns
+    (bounds: bf16 rounding of each entry and a float32 sum of S terms), and
+    reading them launches nothing that the stage's profile counts."""
+    import numpy as np
+
+    from paper_1809_02839_amd import native
+    d, heads, _, S = dims
+    B, dh = 3, d // heads
+    spec = synth.StageSpec("transformer", "bf16", "none", 0, 1, B, 1, dims, 1e-3, 0.9)
+    st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
+    x = torch.from_numpy(synth.stage_input(spec, 0) * 50).cuda().bfloat16()
+    st.profile(True)
+    st.forward(0, x, torch.empty_like(x))
+    before = {k: v["launches"] for k, v in st.profile_read().items()}
+    raw = {i: st.read_stash(0, i) for i in (0, 1, 2, 3)}
+    assert {k: v["launches"] for k, v in st.profile_read().items()} == before
+    st.destroy()
+    p = _bf(raw[2]).reshape(B, heads, S, S)
+    v = _bf(raw[0]).reshape(B, S, 3, heads, dh)[:, :, 2].transpose(0, 2, 1, 3)
+    ctx = _bf(raw[3]).reshape(B, S, heads, dh).transpose(0, 2, 1, 3)
+    want, size = p @ v, p @ np.abs(v)
+    assert np.all(np.abs(ctx - want) <= 2.0 ** -8 * np.abs(want) + S * 2.0 ** -24 * size)
+    f32 = raw[1].view(np.float32).reshape(p.shape)
+    assert np.array_equal(_bf(torch.from_numpy(f32).bfloat16().view(torch.int16).numpy()), p)
