@@ -230,3 +230,33 @@ def test_stash_probabilities_are_the_passes_own(dims):
     assert np.all(np.abs(ctx - want) <= 2.0 ** -8 * np.abs(want) + S * 2.0 ** -24 * size)
     f32 = raw[1].view(np.float32).reshape(p.shape)
     assert np.array_equal(_bf(torch.from_numpy(f32).bfloat16().view(torch.int16).numpy()), p)
+
+
+@pytest.mark.parametrize("S", [56, 264])
+def test_exponential_over_its_range(S):
+    """Scores from 0 down past the exponential's underflow against float64's
+    probabilities. Bounds: two units of 2^-23 for the exponential, one for the
+    division and its product, 2^-24 for each of a lane's S / 2 terms of the sum,
+    and 2^-126 where float32 has no normal numbers."""
+    import numpy as np
+
+    from paper_1809_02839_amd import native
+    d, B = 64, 1
+    spec = synth.StageSpec("transformer", "bf16", "none", 0, 1, B, 1, (d, 1, 72, S), 1e-3, 0.9)
+    W = synth.initial_params(spec)
+    w, b = np.zeros((3 * d, d), np.float32), np.zeros(3 * d, np.float32)
+    b[0] = 8.0                   # q = (8, 0, ...): score = k0 at scale 1 / 8
+    w[d, 0] = 1.0                # k = (x0, 0, ...)
+    W[:w.size], W[w.size:w.size + b.size] = w.ravel(), b
+    x = torch.zeros(B, S, d)
+    x[0, :, 0] = torch.linspace(0.0, -1.0, S) ** 3 * 120.0
+    x = x.bfloat16()
+    st = native.Stage(native.desc_from_spec(spec), W, torch.cuda.current_stream())
+    xg = x.cuda()
+    st.forward(0, xg, torch.empty_like(xg))
+    p = st.read_stash(0, 1).view(np.float32).reshape(S, S).astype(np.float64)
+    st.destroy()
+    e = np.exp(x[0, :, 0].double().numpy())
+    want = e / e.sum()
+    assert np.count_nonzero(want < 2.0 ** -126) >= S // 16 and want.max() > 0.01
+    assert np.all(np.abs(p - want) <= (3 + S / 4) * 2.0 ** -23 * want + 2.0 ** -126)
