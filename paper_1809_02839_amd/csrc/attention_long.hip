@@ -27,7 +27,8 @@
 // of step c and the other operand is read with the same k (frag_cols). So P
 // and dS never go through LDS, a tile costs two barriers, and one 32-column
 // group's values are all that is live: LDS holds the two staged tiles only and
-// three blocks share a CU.
+// three blocks of the forward and dQ (two of dK and dV, which hold two
+// results) share a CU.
 // Rows past the sequence are staged as zeros and their probabilities set to 0.
 #include "kernels.hpp"
 
@@ -428,6 +429,19 @@ __global__ __launch_bounds__(64) void attention_long_probs_kernel(const bf16_t* 
 // holds every (batch, head).
 bool attention_long_supported(int batch, int heads, int head_dim) {
   return (head_dim == 32 || head_dim == 64) && static_cast<long>(batch) * heads <= 65535;
+}
+
+// Where the tiles are faster than the batched GEMMs with stored probabilities.
+// A block walks the whole sequence, so few blocks of a long sequence leave most
+// CUs idle for long, while the GEMMs spread the score matrix over the chip.
+// Both measured, us of an encoder layer's step, tiles / GEMMs, by blocks of 128
+// rows: S = 1024: 64 blocks 363 / 345, 96 349 / 367, 128 354 / 400; S = 2048:
+// 16 466 / 327, 32 411 / 310, 80 486 / 457, 96 490 / 504; S = 4096: 32 758 /
+// 417, 64 765 / 576, 96 775 / 811; S = 10240: 80 1629 / 1646. Up to S = 768 the
+// nine launches are the longer side at any count: S = 640: 10 268 / 308, 40
+// 278 / 298; S = 768: 24 290 / 311.
+bool attention_long_preferred(int batch, int S, int heads) {
+  return S <= 768 || static_cast<long>(batch) * heads * ((S + TS - 1) / TS) >= 88;
 }
 
 hipError_t attention_long_fwd(const bf16_t* qkv, int batch, int S, int heads, int d, float scale, float* stats,

@@ -141,6 +141,7 @@ hipError_t attention_bwd(const bf16_t* qkv, const bf16_t* dctx, const float* sta
 // 64, 128 x 128 score tiles recomputed on chip in both passes. dots: B*heads*S
 // floats of workspace.
 bool attention_long_supported(int batch, int heads, int head_dim);
+bool attention_long_preferred(int batch, int S, int heads);   // else the batched GEMM path is faster
 hipError_t attention_long_fwd(const bf16_t* qkv, int batch, int S, int heads, int d, float scale, float* stats,
                               bf16_t* ctx, hipStream_t s);
 // Probabilities from qkv and the forward's statistics, float32 (Pf) or bf16

@@ -1269,7 +1269,8 @@ void Stage::bwd_bneck(int slot, const void* dy, void* dx) {
 Stage::Attention Stage::attention() const {
   const int B = d_.batch, d = d_.dims[0], Hh = d_.dims[1], S = d_.dims[3];
   if (attention_fused_supported(S, d / Hh, d)) return Attention::kBlock;
-  return attention_long_supported(B, Hh, d / Hh) ? Attention::kTiles : Attention::kGemm;
+  return attention_long_supported(B, Hh, d / Hh) && attention_long_preferred(B, S, Hh) ? Attention::kTiles
+                                                                                       : Attention::kGemm;
 }
 
 void Stage::attention_probs(const bf16_t* qkv, float* scores, float* P, bf16_t* Pb) {

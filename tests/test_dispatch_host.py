@@ -3,8 +3,8 @@
 bf16 GEMM: a workspace that holds exactly the K slices the rule chose gives the
 same count again (the update sums that many partial planes, so a launch that
 took fewer would leave it planes that nobody wrote), and bottleneck stages take
-the slices that fill the CUs. LSTM and float32 GEMM: the rules take the faster
-path where both were measured."""
+the slices that fill the CUs. LSTM, attention and float32 GEMM: the rules take
+the faster path where both were measured."""
 import os
 import subprocess
 
@@ -154,4 +154,24 @@ int main() {
 """ + calls + "}\n", tmp_path).split("\n")
     slower = {p: t for (p, t), g in zip(F32_TIMES.items(), got)
               if t[0 if g.startswith("gemm_f32_short") else 1] > 1.05 * min(t)}
+    assert not slower, slower
+
+
+# us of an encoder layer's step, score tiles against batched GEMMs, by (batch, S,
+# heads) at head dimension 64.
+ATTENTION_TIMES = {
+    (1, 512, 1): (271, 278), (2, 640, 1): (268, 308), (8, 640, 1): (278, 298), (1, 768, 4): (290, 311),
+    (1, 1024, 1): (325, 288), (1, 1024, 4): (331, 299), (1, 1024, 8): (363, 345), (12, 1024, 1): (349, 367),
+    (16, 1024, 1): (354, 400), (1, 2048, 1): (466, 327), (5, 2048, 1): (486, 457), (6, 2048, 1): (490, 504),
+    (1, 2048, 8): (511, 613), (1, 4096, 1): (758, 417), (2, 4096, 1): (765, 576), (3, 4096, 1): (775, 811),
+    (1, 8192, 1): (1337, 1089), (1, 12288, 1): (1921, 2239), (24, 328, 8): (433, 600),
+}
+
+
+@needs_build
+def test_attention_rule_takes_the_faster_path(tmp_path):
+    calls = "".join(f'std::printf("%d\\n", int(attention_long_preferred({b}, {s}, {h})));\n' for b, s, h in ATTENTION_TIMES)
+    got = _run('#include <cstdio>\n#include "kernels.hpp"\nusing namespace spx;\nint main() {\n' + calls + "}\n",
+               tmp_path).split()
+    slower = {c: t for (c, t), g in zip(ATTENTION_TIMES.items(), got) if t[1 - int(g)] > 1.02 * min(t)}
     assert not slower, slower

@@ -260,3 +260,21 @@ def test_exponential_over_its_range(S):
     want = e / e.sum()
     assert np.count_nonzero(want < 2.0 ** -126) >= S // 16 and want.max() > 0.01
     assert np.all(np.abs(p - want) <= (3 + S / 4) * 2.0 ** -23 * want + 2.0 ** -126)
+
+
+# Either side of the line between the score tiles and the batched GEMMs: past
+# 768 positions 88 blocks of 128 rows.
+@pytest.mark.parametrize("batch,S,tiles", [(1, 768, True), (1, 776, False), (13, 776, True), (12, 776, False)])
+def test_attention_rule(batch, S, tiles):
+    from paper_1809_02839_amd import native
+    spec = synth.StageSpec("transformer", "bf16", "none", 0, 1, batch, 1, (64, 1, 72, S, 8), 1e-3, 0.9)
+    st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
+    x = torch.from_numpy(synth.stage_input(spec, 0)).cuda().bfloat16()
+    st.profile(True)
+    st.forward(0, x, torch.empty_like(x))
+    torch.cuda.synchronize()
+    names = set(st.profile_read())
+    st.destroy()
+    assert ("attention_long" in names) == tiles and ("softmax" in names) != tiles, names
+    if batch == 1:
+        _run("transformer", "bf16", "none", 1, 1, (64, 1, 72, S, 8), 1e-3, steps=3)
