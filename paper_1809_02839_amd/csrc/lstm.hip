@@ -286,7 +286,8 @@ hipError_t lstm_step_fwd(const float* zx_t, const bf16_t* h_prev, const bf16_t* 
                          int H, float* gates_t, float* c_t, bf16_t* h_t, hipStream_t s) {
   if (!lstm_step_supported(B, H)) return hipErrorInvalidValue;
   auto* kernel = H % 32 ? lstm_step_fwd_kernel<true> : lstm_step_fwd_kernel<false>;
-  hipLaunchKernelGGL(kernel, dim3(H / FWD_UNITS, (B + FWD_ROWS - 1) / FWD_ROWS), dim3(64 * FWD_WAVES), 0, s, zx_t, h_prev, Wh, c_prev, B, H, gates_t, c_t, h_t);
+  hipLaunchKernelGGL(kernel, dim3(H / FWD_UNITS, (B + FWD_ROWS - 1) / FWD_ROWS), dim3(64 * FWD_WAVES), 0, s, zx_t,
+                     h_prev, Wh, c_prev, B, H, gates_t, c_t, h_t);
   return hipGetLastError();
 }
 
