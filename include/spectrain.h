@@ -188,9 +188,10 @@ int spectrain_stage_backward_noalloc(spectrain_stage_t st, int64_t mb_id, const 
 
 /* The forward of mb_fwd followed by the backward of mb_bwd, with the effect
  * of spectrain_stage_forward then spectrain_stage_backward (same arguments,
- * state rules and results; bitwise but for products of bottleneck stages whose
- * contraction is cut into other slices beside another pass, which sum in
- * another order), the two passes running concurrently on the GPU. In the one-forward-one-backward order of Section 3.1 a stage's
+ * state rules and results; bitwise but for products of bottleneck and bf16
+ * fully connected stages whose contraction is cut into other slices beside
+ * another pass, which sum in another order), the two passes running
+ * concurrently on the GPU. In the one-forward-one-backward order of Section 3.1 a stage's
  * forward is followed by a backward with no update between them, so both
  * passes read weights of the same version (slot 0 and slot 1 as refreshed by
  * the last update, or the mini-batch's weight stash) and neither writes what

@@ -1066,14 +1066,19 @@ constexpr long kCUs = 256;
 //    launches with few 128-wide ones, once used, are slower since the operands
 //    are loaded directly (12544 x 256 x 2304: 28.2 against 23.4 us; 8192 x 512
 //    x 2048: 25.4 against 22.3).
-//  * SPLIT_OCCUPANCY (bottleneck stages): occupancy_splits. The order in which
-//    a product is summed is part of a bottleneck stage's results: its skips
-//    pass every ReLU mask of the outputs undamped to dX and v, and a different
-//    slice count in the 1x1 and 3x3 products moved v of two blocks by up to
-//    3.9e-2 (2-norm) at unchanged error against float64, more than the 3e-2
-//    that two versions of a stage may differ by. It costs: eight blocks at 14 x
-//    14, 64 images, 83.9 against 82.6 ms for 64 mini-batches; two blocks at 7 x
-//    7, 50 images, 48.3 against 48.9 for 96; the smallest stages up to 10 %.
+//  * SPLIT_OCCUPANCY (bottleneck and fully connected stages):
+//    occupancy_splits. The order in which a product is summed shows in these
+//    stages' results: a bottleneck's skips pass every ReLU mask of the outputs
+//    undamped to dX and v, and a fully connected unit's flipped mask moves its
+//    whole row of v. Different slice counts moved v of two blocks by up to
+//    3.9e-2 (2-norm) and single entries of a three-layer stage's v by 0.96 of
+//    themselves, at unchanged error against float64, more than the 3e-2 and
+//    0.95 that two versions of a stage may differ by. It costs: eight blocks at
+//    14 x 14, 64 images, 83.9 against 82.6 ms for 64 mini-batches; two blocks
+//    at 7 x 7, 50 images, 48.3 against 48.9 for 96; the smallest stages up to
+//    10 %; 60 bf16 fully connected stages 0.6 % on average, the worst 18 %
+//    (48 -> 1512 -> 1512 -> 104, 5 rows: 3.0 -> 3.7 ms for 24, 4.8 with the
+//    former 64-wide tiles).
 struct Shape {
   int ksl, splits;
 };

@@ -178,7 +178,7 @@ class Stage {
   // and the update sums them instead of a separate reduction pass.
   void gemm(const GemmDesc& d, bool defer = false);
   SplitRule split_rule() const {
-    if (d_.kind != SPECTRAIN_KIND_BOTTLENECK) return SPLIT_TIMED;
+    if (d_.kind != SPECTRAIN_KIND_BOTTLENECK && d_.kind != SPECTRAIN_KIND_FC) return SPLIT_TIMED;
     return concurrent_ ? SPLIT_OCCUPANCY_SHARED : SPLIT_OCCUPANCY;
   }
   // A weight-gradient GEMM on the side stream: it waits for everything issued

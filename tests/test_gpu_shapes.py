@@ -43,8 +43,8 @@ def test_lstm_steps(head, batch, dims):
     _run("reslstm", "bf16", head, batch, 2, dims, 1e-2)
 
 
-# bf16 products: one tile with K in many slices (the last ones short), few
-# tiles, ragged M, N and K; class counts that are no multiple of 8 (element
+# bf16 products: one tile and few tiles of ragged M, N and K; K in several slices
+# (convolutions); class counts that are no multiple of 8 (element
 # stores) and float32 scores of ragged row counts; a convolution grid inside
 # the 8-wave range (7/8 of the CUs) with a ragged last row tile.
 @pytest.mark.parametrize("kind,head,batch,layers,dims", [
@@ -137,20 +137,24 @@ def test_filter_gradient_planes(batch, dims):
     _run("conv3x3", "bf16", "none", batch, 1, dims, 1e-4)
 
 
-def test_bottleneck_products_keep_their_slices():
-    """A bottleneck's forward products are summed in 2 (1 x 1, K = 1920) and 5
-    (3 x 3, K = 4320) slices, as filling the CUs gives, not the 3 of the time
-    model: another order moves v of two blocks by 3.5e-2 here."""
+# A bottleneck's forward: 2 slices (1 x 1, K = 1920) and 5 (3 x 3, K = 4320), not
+# the 3 of the time model for the first; a fully connected layer: 5 (K = 4104),
+# not 13. Another order moves v by more than two versions may differ.
+@pytest.mark.parametrize("kind,batch,dims,floats", [
+    ("bottleneck", 15, (1920, 480, 8, 8), 960 * 480 * (2 + 5)), ("fc", 50, (4104, 264, 264), 50 * 264 * 5),
+])
+def test_products_keep_their_slices(kind, batch, dims, floats):
     from paper_1809_02839_amd import native
-    spec = synth.StageSpec("bottleneck", "bf16", "none", 0, 1, 15, 1, (1920, 480, 8, 8), 1e-6, 0.9)
+    spec = synth.StageSpec(kind, "bf16", "none", 0, 1, batch, 1, dims, 1e-6, 0.9)
     st = native.Stage(native.desc_from_spec(spec), synth.initial_params(spec), torch.cuda.current_stream())
     x = torch.from_numpy(synth.stage_input(spec, 0)).cuda().bfloat16()
+    y = torch.empty(spec.output_shape(), dtype=torch.bfloat16, device="cuda")
     st.profile(True)
-    st.forward(0, x, torch.empty_like(x))
+    st.forward(0, x, y)
     torch.cuda.synchronize()
     planes = sum(s["extra_bytes_total"] for n, s in st.profile_read().items() if n.startswith("gemm_bf16"))
     st.destroy()
-    assert planes == 4 * 960 * 480 * (2 + 5)
+    assert planes == 4 * floats
 
 
 # Either side of the rule's lines: the largest batch of the fused steps and the
